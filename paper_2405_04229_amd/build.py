@@ -8,6 +8,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcphot.so")
 SOURCES = ["cphot_api.cpp", "cphot_kernels.hip", "cphot_surrogate.hip", "cphot_table.hip"]
+# the propagation kernels are compiled once per block size
+BLOCKS = {"cphot_kernels.hip": ("128", "256", "512", "1024")}
 ARCH = os.environ.get("CPHOT_OFFLOAD_ARCH", "gfx950")
 
 # Packed FP32 instructions stay off: they are avoided on this target. No implicit
@@ -28,12 +30,14 @@ def hipcc() -> str:
 
 
 def build(verbose: bool = False) -> str:
-    """Compiles the sources concurrently (one hipcc per source), then links."""
+    """Compiles the sources concurrently (one hipcc per object), then links."""
     objs, cmds = [], []
     for src in SOURCES:
-        obj = os.path.join(CSRC, src + ".o")
-        cmds.append([hipcc(), *HIP_FLAGS, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj])
-        objs.append(obj)
+        for block in BLOCKS.get(src, ("",)):
+            obj = os.path.join(CSRC, f"{src}{block}.o")
+            define = [f"-DCPHOT_BLOCK={block}"] if block else []
+            cmds.append([hipcc(), *HIP_FLAGS, *define, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj])
+            objs.append(obj)
     if verbose:
         for cmd in cmds:
             print(" ".join(cmd), flush=True)

@@ -237,8 +237,9 @@ int fill_params(const cphot_segments* seg, const cphot_detector* det, cphot::KPa
          !(det->fl_lambda[b] >= d.lambda_min_nm && det->fl_lambda[b] <= d.lambda_max_nm)))
       return fail(CPHOT_ERR_INVALID_ARG, "fluorescence yields must be >= 0 and wavelengths inside the band");
   }
-  p.earth_radius = d.earth_radius;
   p.h_obs = (float)det->h_obs;
+  p.inv_lam_span24 = (p.inv_lam_min - p.inv_lam_max) * 0x1p-24f;
+  p.lam_span24 = (p.lam_max - p.lam_min) * 0x1p-24f;
   p.X_obs = d.profile == CPHOT_PROFILE_LINSLEY5 ? (float)depth(d, det->h_obs) : 0.f;
   p.transport = curved_sur ? cphot::kTransportCurvedSurrogate
                 : curved_tab ? cphot::kTransportCurvedTable
@@ -278,6 +279,20 @@ int fill_params(const cphot_segments* seg, const cphot_detector* det, cphot::KPa
       p.shell_nb_rising = a->nb_rising ? 1 : 0;
     }
   }
+  if (p.n_lam > 0) {
+    p.lam_scale = (float)p.n_lam / (p.lam_max - p.lam_min);
+    p.lam_step = (p.lam_max - p.lam_min) / (float)p.n_lam;
+  }
+  if (curved) {
+    p.Rf = (float)d.earth_radius;
+    p.two_Rf = (float)(2.0 * d.earth_radius);
+    p.r_obs = p.Rf + p.h_obs;
+    p.h_obs1 = (float)(p.obs_layer + 1) * p.dh;
+    p.d_obs1 = (p.h_obs1 - p.h_obs) * (p.two_Rf + p.h_obs1 + p.h_obs);
+    p.two_Rf_dh = p.two_Rf * p.dh;
+    p.inv_dh_walk = 1.0f / p.dh;
+    p.obs_walk = (int)std::floor(p.h_obs / p.dh);
+  }
   const int64_t ns = seg->n_showers;
   if (det->detector == CPHOT_DETECTOR_GRID) {
     if (det->nx < 1 || det->ny < 1 || !finite_pos(det->cell))
@@ -286,6 +301,12 @@ int fill_params(const cphot_segments* seg, const cphot_detector* det, cphot::KPa
     p.cell = (float)det->cell;
     p.inv_cell = (float)(1.0 / det->cell);
     p.inv_cell64 = 1.0 / (double)det->cell;
+    p.half_x = 0.5f * (float)p.nx * p.cell;
+    p.half_y = 0.5f * (float)p.ny * p.cell;
+    p.nx64 = (double)p.nx;
+    p.ny64 = (double)p.ny;
+    p.half_x64 = 0.5 * p.nx64 * (double)p.cell;
+    p.half_y64 = 0.5 * p.ny64 * (double)p.cell;
     p.cuts = need_bins ? det->cuts : 0;  // the parity entry points trace every record
     if (det->transport != CPHOT_TRANSPORT_STRAIGHT && d.n_layers > 0)
       p.cut_e = (float)(a->cut_e[(size_t)p.obs_layer] * (1.0 + 1e-6));
@@ -308,6 +329,8 @@ int fill_params(const cphot_segments* seg, const cphot_detector* det, cphot::KPa
     p.snx = det->snx; p.sny = det->sny;
     p.pitch = (float)det->pitch;
     p.inv_pitch = (float)(1.0 / det->pitch);
+    p.half_x = 0.5f * (float)(p.snx - 1) * p.pitch;
+    p.half_y = 0.5f * (float)(p.sny - 1) * p.pitch;
     p.radius = (float)det->radius;
     p.n_t = det->n_time_bins;
     if (p.n_t < 0) return fail(CPHOT_ERR_INVALID_ARG, "n_time_bins must be >= 0");
@@ -397,64 +420,100 @@ struct LaunchShape {
   size_t lds;
 };
 
-// Launch shape. The grid histogram can be privatised in LDS: the whole grid
-// when it fits, else a window of W x W cells around the grid centre (the core),
-// where most photons of a shower land. Each block then walks a contiguous range
-// of tiles and flushes its window when the shower changes, so global atomics are
-// paid per window cell and block rather than per photon.
-constexpr size_t kLdsBudget = 64 * 1024;  // per block, static + dynamic
-constexpr size_t kLdsPerCu = 160 * 1024;
+// LDS of a CU, and the granule in which a block's share is allocated.
+constexpr size_t kLdsPerCu = 160 * 1024, kLdsGranule = 1280;
 
-// LDS a block may hold while a CU still runs four waves per SIMD (the occupancy
-// the exact tracers' registers allow; kernels with more registers run fewer
-// waves and are then only more conservative): 160 KB over 16 / (BS / 64) blocks.
-size_t lds_at_four_waves(int bs) {
-  const int blocks = std::max(1, 16 / (bs / 64));
-  return kLdsPerCu / (size_t)blocks - 1024;  // margin for the allocation granule
+// LDS that each of `blocks` blocks can hold when a CU runs them together.
+size_t lds_share(int blocks) { return kLdsPerCu / (size_t)std::max(blocks, 1) / kLdsGranule * kLdsGranule; }
+
+// Largest w x h with the sides' ratio near w : h, at most `area` cells and nx x ny.
+void grow_window(int& w, int& h, int nx, int ny, size_t area) {
+  const double f = std::sqrt((double)area / ((double)w * h));
+  if (f <= 1.0) return;
+  w = std::min(nx, (int)(w * f));
+  h = (int)std::min<size_t>((size_t)ny, area / (size_t)w);
+  if (h == ny) w = (int)std::min<size_t>((size_t)nx, area / (size_t)h);
 }
 
+// Launch shape. Counts are privatised in LDS: a device atomic per photon runs at 1 to 5
+// per ns where showers put many photons into few cells (the 1e4-segment shower: 790 us
+// with device atomics alone, 94 us with an LDS grid). A window holds the whole grid when
+// it fits, else the rectangle around the core where most photons land; each block walks a
+// contiguous range of segments and flushes its window when the shower changes.
+//
+// The library's own shape on a ground grid is one block per CU, as large as the registers
+// allow (16 waves, 12 with the network), because its waves share one window: the window
+// takes all the LDS that the segment slots leave (about 22,000 cells, where four blocks of
+// 256 have 4,800 each), one flush serves 16 waves, and every CU ends with its last wave.
+// Against one block of 256 per 256 segments with device atomics: inclined shower of 1e6
+// segments with the correction table 7.7 -> 2.2 ms, with the network 8.2 -> 3.2 ms.
+//
+// A launch with fewer tiles of 64 segments than waves on the chip shares each tile's
+// record rounds among 2^k units (the tile's set-up is repeated on waves that would idle):
+// k as small as fills the chip, at most 4. 1e4 segments on straight rays, k = 0, 2, 4, 6:
+// 129, 44, 23, 27 us; 2e4 on refracted ones: 135, 53, 38, 55 us.
 int choose_shape(const cphot_detector* det, cphot::KParams& p, int mode, LaunchShape& s) {
-  int bs = det->block_size ? det->block_size : 256;
-  if (bs != 128 && bs != 256 && bs != 512) return fail(CPHOT_ERR_INVALID_ARG, "block_size must be 0, 128, 256 or 512");
+  if (det->block_size != 0 && det->block_size != 128 && det->block_size != 256 && det->block_size != 512)
+    return fail(CPHOT_ERR_INVALID_ARG, "block_size must be 0, 128, 256 or 512");
   if (det->hist_window < 0 || det->hist_window_h < 0)
     return fail(CPHOT_ERR_INVALID_ARG, "hist_window and hist_window_h must be >= 0");
-  size_t lds = 0;
-  p.lds_hist = 0;
+  const bool propagate = mode == cphot::MODE_PROPAGATE, on_grid = p.detector == CPHOT_DETECTOR_GRID;
+  const bool own = propagate && on_grid && det->block_size == 0 && det->grid_blocks <= 0 && det->lds_hist != 0 &&
+                   det->hist_window == 0;
+  const int bs = own ? cphot::kBigBlock : det->block_size ? det->block_size : 256;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) dev = 0;
+  const int64_t cus = cu_count(dev);
+  cphot::KernelInfo info{0, 4};
+  if (propagate && (own || det->lds_hist != 0)) info = cphot::propagate_info(p, bs);
+  const int waves = own ? std::min(16, 4 * info.waves_per_simd) : bs / 64;       // of a block
+  int per_cu = own ? 1 : std::max(1, 4 * std::min(info.waves_per_simd, 4) / waves);  // resident blocks
+  p.lds_hist = p.hist_auto = p.hist_words = p.sub_shift = 0;
   p.hist_w = p.hist_h = p.hist_x0 = p.hist_y0 = p.hist_tw = 0;
-  const size_t stat =
-      (mode == cphot::MODE_PROPAGATE && det->lds_hist != 0) ? cphot::propagate_static_lds(p, mode, bs) : 0;
-  if (mode == cphot::MODE_PROPAGATE && p.detector == CPHOT_DETECTOR_GRID && det->lds_hist != 0) {
-    const size_t room = stat < kLdsBudget ? (kLdsBudget - stat) / 4 : 0;  // cells that fit
+  if (propagate && on_grid && det->lds_hist != 0) {
+    // cells of a block's window when `blocks` of them run on a CU
+    auto room = [&](int blocks) {
+      const size_t share = lds_share(blocks);
+      return share > info.lds ? (share - info.lds) / 4 : (size_t)0;
+    };
+    const size_t whole = (size_t)p.nx * p.ny;
     int w = p.nx, h = p.ny;
     if (det->hist_window > 0) {
-      // the caller's window, shrunk (longer side first) until it fits
+      // the caller's window, shrunk (longer side first) until it fits beside two waves per SIMD
       w = std::min(p.nx, det->hist_window);
       h = std::min(p.ny, det->hist_window_h > 0 ? det->hist_window_h : det->hist_window);
-      while ((size_t)w * h > room && w > 0 && h > 0) {
+      const size_t most = room(std::max(1, std::min(per_cu, 8 / waves)));
+      while ((size_t)w * h > most && w > 0 && h > 0) {
         if (w >= h) --w;
         else --h;
       }
-    } else if ((size_t)w * h > room) {
-      int side = (int)std::sqrt((double)room);
-      while (side > 0 && (size_t)side * side > room) --side;
-      w = std::min(p.nx, side);
-      h = std::min(p.ny, side);
+      // and grown again into LDS that the blocks resident with it would leave unused,
+      // where each block has the segments to pay for the larger flush
+      while (per_cu > 1 && (size_t)w * h > room(per_cu)) --per_cu;
+      const int64_t blocks = det->grid_blocks > 0 ? det->grid_blocks : cus * per_cu;
+      const size_t worth = (size_t)(p.n / std::max<int64_t>(blocks, 1)) * 4;
+      if (w > 0 && h > 0) grow_window(w, h, p.nx, p.ny, std::min(room(per_cu), worth));
+    } else {
+      while (per_cu > 1 && room(per_cu) < std::min<size_t>(whole, 4096)) --per_cu;
+      const size_t area = room(per_cu);
+      if (whole > area) {
+        if (own) p.hist_auto = (int32_t)area;
+        const int side = (int)std::sqrt((double)area);
+        w = std::min(p.nx, side);
+        h = std::min(p.ny, side);
+      }
     }
-    const bool usable = w >= 8 && h >= 8 && (size_t)w * h <= room;
+    const bool usable = w >= 8 && h >= 8;
     if (det->lds_hist == 1 && !usable) return fail(CPHOT_ERR_INVALID_ARG, "no LDS histogram window fits this launch");
-    // Library choice: the whole grid when it fits; a partial window only for
-    // straight rays, where a record costs about as much as its global atomic.
-    // Refracting transports spend far more per record and lose more to the
-    // window's lower occupancy than they save in atomics (the autotuner times both).
-    const bool whole = w == p.nx && h == p.ny;
-    const bool wanted = det->lds_hist == 1 || whole || p.transport == CPHOT_TRANSPORT_STRAIGHT;
-    if (usable && wanted) {
+    if (usable) {
       p.lds_hist = 1;
       p.hist_w = w;
       p.hist_h = h;
       p.hist_x0 = std::min(std::max((p.nx - w) / 2 + det->hist_window_dx, 0), p.nx - w);
       p.hist_y0 = std::min(std::max((p.ny - h) / 2 + det->hist_window_dy, 0), p.ny - h);
-      lds = (size_t)w * h * 4;
+      p.hist_words = p.hist_auto ? p.hist_auto : w * h;
+    } else {
+      p.hist_auto = 0;
     }
   }
   // spheres: the whole array of sphere counts in LDS when it fits (hits cluster
@@ -463,8 +522,9 @@ int choose_shape(const cphot_detector* det, cphot::KParams& p, int mode, LaunchS
   // near the core arrive (delays after the plane front of a few to tens of ns);
   // later bins stay global. The time part takes only the LDS that leaves the
   // occupancy the kernel's registers allow.
-  if (mode == cphot::MODE_PROPAGATE && p.detector == CPHOT_DETECTOR_SPHERES && det->lds_hist != 0) {
-    const size_t room = stat < kLdsBudget ? (kLdsBudget - stat) / 4 : 0;
+  if (propagate && !on_grid && det->lds_hist != 0) {
+    const size_t most = lds_share(std::max(1, std::min(per_cu, 8 / waves)));
+    const size_t room = info.lds < most ? (most - info.lds) / 4 : 0;
     const size_t nsph = (size_t)p.snx * p.sny;
     if (nsph > room) {
       if (det->lds_hist == 1) return fail(CPHOT_ERR_INVALID_ARG, "the sphere counts do not fit in LDS");
@@ -472,28 +532,27 @@ int choose_shape(const cphot_detector* det, cphot::KParams& p, int mode, LaunchS
       p.lds_hist = 1;
       p.hist_w = p.snx;
       p.hist_h = p.sny;
-      const size_t cap = std::min(kLdsBudget, lds_at_four_waves(bs));
-      if (p.n_t > 0 && cap > stat + nsph * 4) {
-        const size_t tb = std::min((cap - stat) / 4 - nsph, room - nsph) / nsph;
+      const size_t cap = lds_share(per_cu);
+      if (p.n_t > 0 && cap > info.lds + nsph * 4) {
+        const size_t tb = std::min((cap - info.lds) / 4 - nsph, room - nsph) / nsph;
         p.hist_tw = (int)std::min<size_t>(tb, (size_t)p.n_t + 1);
       }
-      lds = nsph * (1 + (size_t)p.hist_tw) * 4;
+      p.hist_words = (int32_t)(nsph * (1 + (size_t)p.hist_tw));
     }
   }
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-  const int64_t tiles = (p.n + bs - 1) / bs;
-  // One block per tile lets the dispatcher balance uneven tiles. With an LDS
-  // histogram a persistent grid (a few blocks per CU, each over a contiguous
-  // range of tiles) amortises the window's zeroing and flushes.
-  // Sphere counts are few, so their flush stays cheap at one block per tile.
-  const bool persistent = p.lds_hist && p.detector == CPHOT_DETECTOR_GRID;
-  int64_t g = det->grid_blocks > 0 ? det->grid_blocks : (persistent ? (int64_t)cu_count(dev) * 4 : tiles);
-  if (g > tiles) g = tiles;
+  const int64_t tiles = (p.n + 63) / 64;
+  const int64_t fill = cus * per_cu * waves;  // waves on the chip
+  while (mode != cphot::MODE_COUNTS && p.sub_shift < 4 && (tiles << p.sub_shift) < fill) ++p.sub_shift;
+  const int64_t most = ((tiles << p.sub_shift) + waves - 1) / waves;
+  // a persistent grid fills the chip once and amortises the tables and the window; without
+  // LDS counts one unit per wave lets the dispatcher balance uneven tiles
+  int64_t g = det->grid_blocks > 0 ? det->grid_blocks : (p.hist_words ? cus * per_cu : most);
+  if (mode == cphot::MODE_COUNTS) g = std::min<int64_t>((p.n + 255) / 256, det->grid_blocks > 0 ? det->grid_blocks : cus * 8);
+  else if (g > most) g = most;
   if (g < 1) g = 1;
   s.block = bs;
   s.grid = (int)g;
-  s.lds = lds;
+  s.lds = (size_t)p.hist_words * 4;
   return CPHOT_OK;
 }
 
@@ -1180,8 +1239,8 @@ int cphot_autotune(const cphot_segments* seg, const cphot_detector* det, cphot_b
           d.block_size = bs;
           cphot::KParams p;
           if ((rc = fill_params(seg, &d, p, true, out))) break;
-          const size_t stat = cphot::propagate_static_lds(p, cphot::MODE_PROPAGATE, bs);
-          const size_t room = stat < kLdsBudget ? (kLdsBudget - stat) / 4 : 0;
+          const size_t stat = cphot::propagate_info(p, bs).lds, most = lds_share(std::max(1, 512 / bs));
+          const size_t room = stat < most ? (most - stat) / 4 : 0;
           for (size_t area : {(size_t)2304, (size_t)4096, (size_t)9216, room}) {
             Window f;
             if (area <= room && fit_window(foot, det->nx, det->ny, area, f)) wins.push_back(f);

@@ -35,6 +35,40 @@ __device__ __forceinline__ uint4 philox(uint32_t c0, uint32_t c1, uint32_t c2, u
   return make_uint4(c0, c1, c2, c3);
 }
 
+// The rounds of a record's Philox block that depend on its segment alone. A record's
+// counter is (k, id low, id high, tag): in the first round the product with id high, in
+// the second the product with the first round's word 0 are the segment's. Returns
+// (c1 ^ k0 of round 2, hi(product) ^ k1 of round 2, lo(product)).
+__device__ __forceinline__ uint3 philox_segment(uint32_t id_lo, uint32_t id_hi, uint32_t k0, uint32_t k1) {
+  const uint64_t p1 = (uint64_t)0xCD9E8D57u * id_hi;
+  const uint32_t n0 = (uint32_t)(p1 >> 32) ^ id_lo ^ k0;
+  const uint64_t p0 = (uint64_t)0xD2511F53u * n0;
+  return make_uint3((uint32_t)p1 ^ (k0 + 0x9E3779B9u), (uint32_t)(p0 >> 32) ^ (k1 + 0xBB67AE85u), (uint32_t)p0);
+}
+
+// a ^ b ^ c in one instruction.
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
+// philox(k, id low, id high, tag) from the segment's words (x, y, z of `s`, bit patterns).
+__device__ __forceinline__ uint4 philox_record(const float4 s, uint32_t k, uint32_t tag, uint32_t k0, uint32_t k1) {
+  const uint64_t p0 = (uint64_t)0xD2511F53u * k;
+  const uint64_t p1 = (uint64_t)0xCD9E8D57u * xor3((uint32_t)(p0 >> 32), tag, k1);
+  uint32_t c0 = (uint32_t)(p1 >> 32) ^ __float_as_uint(s.x), c1 = (uint32_t)p1;
+  uint32_t c2 = (uint32_t)p0 ^ __float_as_uint(s.y), c3 = __float_as_uint(s.z);
+#pragma unroll
+  for (int r = 2; r < 10; ++r) {
+    const uint64_t q0 = (uint64_t)0xD2511F53u * c0;
+    const uint64_t q1 = (uint64_t)0xCD9E8D57u * c2;
+    c0 = xor3((uint32_t)(q1 >> 32), c1, k0 + (uint32_t)r * 0x9E3779B9u);
+    c2 = xor3((uint32_t)(q0 >> 32), c3, k1 + (uint32_t)r * 0xBB67AE85u);
+    c1 = (uint32_t)q1;
+    c3 = (uint32_t)q0;
+  }
+  return make_uint4(c0, c1, c2, c3);
+}
+
 // Hardware reciprocal and square root (about 1 ulp for the normal, positive
 // inputs they get here) where the correctly rounded sequences cost about ten
 // instructions; used on the per-photon planar path, whose tolerances are far
@@ -100,69 +134,68 @@ __device__ inline int64_t poisson_count(double mu, uint32_t w0, uint64_t id, uin
 }
 
 // Random word -> uniform on [0, 1) with 24 bits (exact in FP32).
-__device__ __forceinline__ float u24(uint32_t w) { return (float)(w >> 8) * 5.9604644775390625e-8f; }
+constexpr float kU24 = 5.9604644775390625e-8f;  // 2^-24
+__device__ __forceinline__ float u24(uint32_t w) { return (float)(w >> 8) * kU24; }
 
-template <int BS>
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s_wave, uint32_t& total) {
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  uint32_t x = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t y = __shfl_up(x, d, 64);
-    if (lane >= d) x += y;
-  }
-  if (lane == 63) s_wave[wid] = x;
-  __syncthreads();
-  uint32_t pre = 0, tot = 0;
-#pragma unroll
-  for (int q = 0; q < BS / 64; ++q) {
-    const uint32_t t = s_wave[q];
-    pre += (q < wid) ? t : 0u;
-    tot += t;
-  }
-  total = tot;
-  return pre + x - v;
+// One step of a wave-wide scan: the value `ctrl` lanes below (DPP row shifts and
+// broadcasts, no LDS), 0 where there is none.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp0(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
 }
 
-// Two exclusive block scans at once (one barrier): returns the exclusive prefixes
-// of a and b, and their block totals. s_wave holds 2 * BS / 64 entries.
-template <int BS>
-__device__ __forceinline__ uint2 block_exclusive_scan2(uint32_t a, uint32_t b, uint32_t* s_wave, uint32_t& total_a,
-                                                      uint32_t& total_b) {
-  constexpr int kWaves = BS / 64;
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  uint32_t x = a, y = b;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t xu = __shfl_up(x, d, 64), yu = __shfl_up(y, d, 64);
-    if (lane >= d) {
-      x += xu;
-      y += yu;
-    }
-  }
-  if (lane == 63) {
-    s_wave[wid] = x;
-    s_wave[kWaves + wid] = y;
-  }
-  __syncthreads();
-  uint32_t pa = 0, pb = 0, ta = 0, tb = 0;
-#pragma unroll
-  for (int q = 0; q < kWaves; ++q) {
-    const uint32_t u = s_wave[q], v = s_wave[kWaves + q];
-    pa += (q < wid) ? u : 0u;
-    pb += (q < wid) ? v : 0u;
-    ta += u;
-    tb += v;
-  }
-  total_a = ta;
-  total_b = tb;
-  return make_uint2(pa + x - a, pb + y - b);
-}
-
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+// Inclusive sum over the lanes up to this one.
+__device__ __forceinline__ uint32_t wave_scan_add(uint32_t v) {
+  v += dpp0<0x111, 0xf>(v);
+  v += dpp0<0x112, 0xf>(v);
+  v += dpp0<0x114, 0xf>(v);
+  v += dpp0<0x118, 0xf>(v);
+  v += dpp0<0x142, 0xa>(v);
+  v += dpp0<0x143, 0xc>(v);
   return v;
+}
+
+// Inclusive maximum over the lanes up to this one.
+__device__ __forceinline__ uint32_t wave_scan_max(uint32_t v) {
+  v = max(v, dpp0<0x111, 0xf>(v));
+  v = max(v, dpp0<0x112, 0xf>(v));
+  v = max(v, dpp0<0x114, 0xf>(v));
+  v = max(v, dpp0<0x118, 0xf>(v));
+  v = max(v, dpp0<0x142, 0xa>(v));
+  v = max(v, dpp0<0x143, 0xc>(v));
+  return v;
+}
+
+// Sum over the wave, the same in every lane.
+__device__ __forceinline__ uint32_t wave_total(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_add(v), 63);
+}
+
+// Position of this lane when the wave's lanes are ordered by (key, lane), key < 2^BITS:
+// bit by bit from the top, the lanes that still agree with this one and have a 0 where it
+// has a 1 come before it.
+template <int BITS>
+__device__ __forceinline__ uint32_t wave_rank(uint32_t key) {
+  uint64_t same = ~0ull;
+  uint32_t rank = 0;
+#pragma unroll
+  for (int b = BITS - 1; b >= 0; --b) {
+    const bool one = (key >> b) & 1u;
+    const uint64_t ones = __ballot(one);
+    const uint64_t low = same & ~ones;
+    rank += one ? (uint32_t)__popcll(low) : 0u;
+    same = one ? same & ones : low;
+  }
+  const uint32_t lo = (uint32_t)same, hi = (uint32_t)(same >> 32);
+  return rank + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+}
+
+// Orders the LDS accesses of one wave's lanes before and after this point (the
+// wave's LDS operations complete in order; no other wave shares what is ordered).
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
 
@@ -383,10 +416,9 @@ __device__ __forceinline__ void layer_series(const float4* __restrict__ lay, con
 // a sum of terms no larger than the path itself: FP32 carries it to about 1e-7 of
 // the displacement (a few mm over tens of km), with no radius-sized value
 // subtracted; A = P + (A - P) is formed in FP64 for the binning.
-__device__ __forceinline__ void curved_arrival(double Re, float h_obs, float Px, float Py, float Pz, float h0,
+__device__ __forceinline__ void curved_arrival(float Rf, float h_obs, float r1, float Px, float Py, float Pz, float h0,
                                                float ux, float uy, float uz, float psi, float across, double& ax,
                                                double& ay, double& az) {
-  const float Rf = (float)Re;
   const float rq = Rf + h0;  // |P - C| (its rounding scales e_r by 1 +- 6e-8)
   const float irq = rcp_fast(rq);
   // e_r = (Px, Py, Pz + R) / rq, its z component kept as 1 + ez1 (Pz + R - rq = Pz - h0)
@@ -415,7 +447,6 @@ __device__ __forceinline__ void curved_arrival(double Re, float h_obs, float Px,
     sps = sinf(psi);
     omc = 2.0f * sh * sh;
   }
-  const float r1 = Rf + h_obs;
   const float rad = -fmaf(r1, omc, h0 - h_obs);  // along e_r
   const float tan = r1 * sps;                    // along e_t
   float dx = fmaf(rad, erx, tan * tx), dy = fmaf(rad, ery, tan * ty), dz = fmaf(rad, ez1, fmaf(tan, tz, rad));
@@ -437,11 +468,11 @@ struct CurvedWalk {
 };
 
 template <bool NEED_TIME>
-__device__ __forceinline__ void curved_walk(const float4* __restrict__ lay, float2 sp, float dh, int n_layers,
-                                            float h_obs, double Re, float Px, float Py, float Pz, float h0,
-                                            float ux, float uy, float uz, float axx, float axy, float axz,
-                                            CurvedWalk& w) {
-  const float Rf = (float)Re, twoR = (float)(2.0 * Re);
+__device__ __forceinline__ void curved_walk(const float4* __restrict__ lay, float2 sp, const KParams& k, float Px,
+                                            float Py, float Pz, float h0, float ux, float uy, float uz, float axx,
+                                            float axy, float axz, CurvedWalk& w) {
+  const float Rf = k.Rf, twoR = k.two_Rf, dh = k.dh, h_obs = k.h_obs;
+  const int n_layers = k.n_layers;
   // emission frame: radial e_r, tangent e_t (photon's horizontal direction), normal e_n
   const float qz = Pz + Rf;
   const float rq = sqrt_fast(fmaf(Px, Px, fmaf(Py, Py, qz * qz)));
@@ -467,8 +498,8 @@ __device__ __forceinline__ void curved_walk(const float4* __restrict__ lay, floa
     a_t = fmaf(axx, etx, fmaf(axy, ety, axz * etz));
     a_n = fmaf(axx, enx, fmaf(axy, eny, axz * enz));
   }
-  int i = min((int)(h0 * (1.0f / dh)), n_layers - 1);
-  const int obs = (int)floorf(h_obs / dh);
+  int i = min((int)(h0 * k.inv_dh_walk), n_layers - 1);
+  const int obs = k.obs_walk;
   const float A = Rf + h0;
   const float c1 = mu * mu / (1.0f + s0);  // 1 - s_0
   const float d0 = lay[i].x;
@@ -560,7 +591,7 @@ __device__ __forceinline__ void curved_walk(const float4* __restrict__ lay, floa
   w.opt = opt;
   w.arrived = arrived;
   if (arrived) {
-    curved_arrival(Re, h_obs, Px, Py, Pz, h0, ux, uy, uz, (float)psi, 0.f, w.ax, w.ay, w.az);
+    curved_arrival(Rf, h_obs, k.r_obs, Px, Py, Pz, h0, ux, uy, uz, (float)psi, 0.f, w.ax, w.ay, w.az);
   } else {  // left the atmosphere: no arrival point
     w.ax = (double)Px;
     w.ay = (double)Py;
@@ -611,47 +642,49 @@ __device__ __forceinline__ float shell_acc4(float4 v, float b0, float b1, float 
   return fmaf(v.w, b3, fmaf(v.z, b2, fmaf(v.y, b1, fmaf(v.x, b0, s))));
 }
 
-template <bool NEED_TIME>
-__device__ __forceinline__ bool curved_series(const float4* __restrict__ lay, const float* __restrict__ rows,
-                                              float2 sp, float dh, int n_layers, int obs, float h_obs, double Re,
-                                              float rho_max, float t_max, bool nb_rising, float Px, float Py,
-                                              float Pz, float h0,
-                                              float ux, float uy, float uz, float axx, float axy, float axz,
-                                              CurvedWalk& w) {
-  const float Rf = (float)Re, twoR = (float)(2.0 * Re);
+__device__ __forceinline__ float shell_acc3(float4 v, float b0, float b1, float b2, float s) {
+  return fmaf(v.z, b2, fmaf(v.y, b1, fmaf(v.x, b0, s)));
+}
+
+// The three values exist here: nothing that leads to them is moved past this point.
+__device__ __forceinline__ void pin(float& a, float& b, float& c) { asm volatile("" : "+v"(a), "+v"(b), "+v"(c)); }
+
+template <bool NEED_TIME, class K>
+__device__ __forceinline__ bool curved_series(const float4* __restrict__ lay, const K& k, const KParams& cold,
+                                              const float4 rc,
+                                              float2 sp, float Px, float Py, float Pz, float rq, float h0, float ux,
+                                              float uy, float uz, float axx, float axy, float axz, CurvedWalk& w) {
+  const float Rf = k.Rf, twoR = k.two_Rf, h_obs = k.h_obs, dh = k.dh;
+  const int obs = k.obs_layer;
   const float qz = Pz + Rf;
-  const float rq = sqrt_fast(fmaf(Px, Px, fmaf(Py, Py, qz * qz)));
   const float irq = rcp_fast(rq);
   const float erx = Px * irq, ery = Py * irq, erz = qz * irq;
   const float mu = fmaf(ux, erx, fmaf(uy, ery, uz * erz));
   const float c0 = -mu;
-  if (!(c0 > 0.f)) return false;
   const float etx0 = fmaf(-mu, erx, ux), ety0 = fmaf(-mu, ery, uy), etz0 = fmaf(-mu, erz, uz);
   const float s0 = sqrt_fast(fmaf(etx0, etx0, fmaf(ety0, ety0, etz0 * etz0)));
-  const int j = min((int)(h0 * (1.0f / dh)), n_layers - 1);
+  const int j = min((int)(h0 * k.inv_dh_walk), k.n_layers - 1);
   const float r0 = Rf + h0;
   const float rc0 = r0 * c0, p = r0 * s0;
   const float G0 = rc0 * rc0;
-  const float robs = Rf + h_obs;
+  const float robs = k.r_obs;
   // straight chord from r0 to the observation sphere
   const float dO = (h0 - h_obs) * (twoR + h0 + h_obs);
   const float Gobs = G0 - dO;
   const float4 Lj = lay[j];
-  if (!(Gobs > 0.f)) {
+  if (!(c0 > 0.f && Gobs > 0.f)) {
     // The straight line misses the observation sphere. Refraction bends the ray
     // down, and it reaches the sphere iff its impact parameter in every shell,
     // n_j p / n_i, stays below that shell's lower radius (b_i, r_obs in the
     // observation shell); with n_i b_i increasing in i the binding shells are the
     // observation shell and the one above it. Rays failing this turn round above
     // the sphere and leave the atmosphere: they never arrive (no walk needed).
-    if (!nb_rising) return false;
     const float gap = (h0 - h_obs) - r0 * (c0 * c0) * rcp_fast(1.0f + s0);  // p - r_obs
     float g = 0.f;                                                          // bound on p - r_obs
     if (j > obs) {
-      const float hb1 = (float)(obs + 1) * dh - h_obs;                     // b_{obs+1} - r_obs
+      const float hb1 = cold.h_obs1 - cold.h_obs;                           // b_{obs+1} - r_obs
       g = fminf(robs * ((lay[obs].x - Lj.x) * Lj.y), fmaf(robs + hb1, (lay[obs + 1].x - Lj.x) * Lj.y, hb1));
     }
-    if (gap < g) return false;  // bent onto the sphere: the shell walk traces it
     w.tau = 0.f;
     w.geo = 0.f;
     w.opt = 0.f;
@@ -659,96 +692,104 @@ __device__ __forceinline__ bool curved_series(const float4* __restrict__ lay, co
     w.ax = (double)Px;  // no arrival point
     w.ay = (double)Py;
     w.az = (double)Pz;
-    return true;
+    // bent onto the sphere, or going up: the shell walk traces it
+    return c0 > 0.f && cold.shell_nb_rising && !(gap < g);
   }
   const float Ls = dO * rcp_fast(rc0 + sqrt_fast(Gobs));
   const float extj = fmaf(Lj.z, sp.x, Lj.w * sp.y);
-  float tau, dpsi = 0.f, dL = 0.f, opt = 0.f;
-  if (j <= obs) {
-    tau = extj * Ls;
-    if constexpr (NEED_TIME) opt = Lj.x * Ls;
-  } else {
-    const float hj = (float)j * dh, ho1 = (float)(obs + 1) * dh;
+  float tau, dpsi, dL = 0.f, opt = 0.f;
+  // a start inside the observation shell (straight all the way) takes the same
+  // instructions and drops their results: nearly every record starts above it
+  const bool inside = j <= obs;
+  {
+    const float hj = (float)j * dh, ho1 = k.h_obs1;
     const float dJ = (h0 - hj) * (twoR + h0 + hj);           // r0^2 - b_j^2
     const float Gj = G0 - dJ;
     const float DO = (hj - h_obs) * (twoR + hj + h_obs);     // b_j^2 - r_obs^2
     const float iG = rcp_fast(Gj);
     const float t = (p * p) * iG;
-    if (!(DO * iG <= rho_max && t <= t_max)) return false;
+    if (!inside && !(DO * iG <= k.shell_rho && t <= k.shell_tmax)) return false;
     const float sG = sqrt_fast(Gj);
-    const float gam = (twoR * dh) * iG;
+    const float gam = k.two_Rf_dh * iG;
     // basis sqrt(G_j) t^k gam^m of the 15 terms, taken four at a time against the
-    // rows' float4 groups (few live registers): q = 0..4 (k 0, m 1..5), 5..9 (k 1,
-    // m 1..5), 10..12 (k 2, m 1..3), 13..14 (k 3, m 1..2)
+    // rows' float4 groups: q = 0..4 (k 0, m 1..5), 5..9 (k 1, m 1..5), 10..12 (k 2,
+    // m 1..3), 13..14 (k 3, m 1..2)
     const float g1 = sG * gam, g2 = g1 * gam, g3 = g2 * gam, g4 = g3 * gam, g5 = g4 * gam;
     const float t2 = t * t, t3 = t2 * t;
-    const float* r = rows + (size_t)j * kShellRow;
-    const float4* r4 = reinterpret_cast<const float4*>(r);
+    const float4* r4 = reinterpret_cast<const float4*>(k.shells + (size_t)j * kShellRow);
     float sR = 0.f, sA = 0.f, sPe = 0.f, sP1 = 0.f, sL = 0.f, sD = 0.f;
+    // A group's loads are issued together, and its products pinned behind them. Left to
+    // itself the compiler issues one load at a time and waits for each (15 exposed cache
+    // latencies a record), and moves the extinction sums to their late use, where the row
+    // would hold 32 registers.
     {
-      const float b0 = g1, b1 = g2, b2 = g3, b3 = g4;
-      sR = shell_acc4(r4[0], b0, b1, b2, b3, sR);
-      sA = shell_acc4(r4[4], b0, b1, b2, b3, sA);
-      sPe = shell_acc4(r4[8], b0, b1, b2, b3, sPe);
-      if constexpr (NEED_TIME) sD = shell_acc4(r4[20], b0, b1, b2, b3, sD);
+      const float4 vR = r4[0], vA = r4[4], vPe = r4[8];
+      sR = shell_acc4(vR, g1, g2, g3, g4, sR);
+      sA = shell_acc4(vA, g1, g2, g3, g4, sA);
+      sPe = shell_acc4(vPe, g1, g2, g3, g4, sPe);
+      if constexpr (NEED_TIME) sD = shell_acc4(r4[20], g1, g2, g3, g4, sD);
     }
-    // the groups' loads stay with their products: hoisting all of them would hold
-    // 64 (96 with the delay) table values at once
-    __builtin_amdgcn_sched_barrier(0);
+    pin(sR, sA, sPe);
     {
-      const float b0 = g5, b1 = t * g1, b2 = t * g2, b3 = t * g3;
-      sR = shell_acc4(r4[1], b0, b1, b2, b3, sR);
-      sA = shell_acc4(r4[5], b0, b1, b2, b3, sA);
-      sPe = shell_acc4(r4[9], b0, b1, b2, b3, sPe);
-      sP1 = shell_acc4(r4[13], b0, b1, b2, b3, sP1);
+      const float4 vR = r4[1], vA = r4[5], vPe = r4[9], vP1 = r4[13];
+      const float e1 = t * g1, e2 = t * g2, e3 = t * g3;
+      sR = shell_acc4(vR, g5, e1, e2, e3, sR);
+      sA = shell_acc4(vA, g5, e1, e2, e3, sA);
+      sPe = shell_acc4(vPe, g5, e1, e2, e3, sPe);
+      sP1 = shell_acc4(vP1, g5, e1, e2, e3, sP1);
       if constexpr (NEED_TIME) {
-        sL = shell_acc4(r4[17], b0, b1, b2, b3, sL);
-        sD = shell_acc4(r4[21], b0, b1, b2, b3, sD);
+        sL = shell_acc4(r4[17], g5, e1, e2, e3, sL);
+        sD = shell_acc4(r4[21], g5, e1, e2, e3, sD);
       }
     }
-    __builtin_amdgcn_sched_barrier(0);
+    pin(sR, sA, sPe);
     {
-      const float b0 = t * g4, b1 = t * g5, b2 = t2 * g1, b3 = t2 * g2;
-      sR = shell_acc4(r4[2], b0, b1, b2, b3, sR);
-      sA = shell_acc4(r4[6], b0, b1, b2, b3, sA);
-      sPe = shell_acc4(r4[10], b0, b1, b2, b3, sPe);
-      sP1 = shell_acc4(r4[14], b0, b1, b2, b3, sP1);
+      const float4 vR = r4[2], vA = r4[6], vPe = r4[10], vP1 = r4[14];
+      const float e0 = t * g4, e1 = t * g5, e2 = t2 * g1, e3 = t2 * g2;
+      sR = shell_acc4(vR, e0, e1, e2, e3, sR);
+      sA = shell_acc4(vA, e0, e1, e2, e3, sA);
+      sPe = shell_acc4(vPe, e0, e1, e2, e3, sPe);
+      sP1 = shell_acc4(vP1, e0, e1, e2, e3, sP1);
       if constexpr (NEED_TIME) {
-        sL = shell_acc4(r4[18], b0, b1, b2, b3, sL);
-        sD = shell_acc4(r4[22], b0, b1, b2, b3, sD);
+        sL = shell_acc4(r4[18], e0, e1, e2, e3, sL);
+        sD = shell_acc4(r4[22], e0, e1, e2, e3, sD);
       }
     }
-    __builtin_amdgcn_sched_barrier(0);
+    pin(sR, sA, sPe);
     {
-      const float b0 = t2 * g3, b1 = t3 * g1, b2 = t3 * g2;  // the groups' fourth entries are zero
-      sR = shell_acc4(r4[3], b0, b1, b2, 0.f, sR);
-      sA = shell_acc4(r4[7], b0, b1, b2, 0.f, sA);
-      sPe = shell_acc4(r4[11], b0, b1, b2, 0.f, sPe);
-      sP1 = shell_acc4(r4[15], b0, b1, b2, 0.f, sP1);
+      const float4 vR = r4[3], vA = r4[7], vPe = r4[11], vP1 = r4[15];  // (fourth entries: zero)
+      const float e0 = t2 * g3, e1 = t3 * g1, e2 = t3 * g2;
+      sR = shell_acc3(vR, e0, e1, e2, sR);
+      sA = shell_acc3(vA, e0, e1, e2, sA);
+      sPe = shell_acc3(vPe, e0, e1, e2, sPe);
+      sP1 = shell_acc3(vP1, e0, e1, e2, sP1);
       if constexpr (NEED_TIME) {
-        sL = shell_acc4(r4[19], b0, b1, b2, 0.f, sL);
-        sD = shell_acc4(r4[23], b0, b1, b2, 0.f, sD);
+        sL = shell_acc3(r4[19], e0, e1, e2, sL);
+        sD = shell_acc3(r4[23], e0, e1, e2, sD);
       }
     }
+    pin(sR, sA, sPe);
     // partial start shell (straight: u = 0 there) and partial observation shell
     const float lS = dJ * rcp_fast(rc0 + sG);
     const float4 Lo = lay[obs];
     const float eO = (Lo.x - Lj.x) * Lo.y;
     const float dd = (p * p) * (eO * (2.0f - eO));
-    const float num = (ho1 - h_obs) * (twoR + ho1 + h_obs);  // b_{obs+1}^2 - r_obs^2
+    const float num = k.d_obs1;  // b_{obs+1}^2 - r_obs^2
     const float A0 = Gj - (hj - ho1) * (twoR + hj + ho1), B0 = Gj - DO;
     const float qA = sqrt_fast(A0 + dd), qA0 = sqrt_fast(A0), qB = sqrt_fast(B0 + dd), qB0 = sqrt_fast(B0);
     const float lO = num * rcp_fast(qA + qB), lOs = num * rcp_fast(qA0 + qB0);
     const float dlO = -dd * (lO + lOs) * rcp_fast((qA + qA0) * (qB + qB0));  // lO - lOs
     tau = fmaf(extj, lS, fmaf(sp.x, sR, fmaf(sp.y, sA, fmaf(Lo.z, sp.x, Lo.w * sp.y) * lO)));
-    dpsi = p * ((sP1 - sPe) * rcp_fast(Rf * Rf) + (dlO - eO * lO) * rcp_fast((Rf + ho1) * robs));
+    dpsi = p * ((sP1 - sPe) * rc.y + (dlO - eO * lO) * rc.z);
+    tau = inside ? extj * Ls : tau;
+    dpsi = inside ? 0.f : dpsi;
     if constexpr (NEED_TIME) {
-      dL = sL + dlO;
-      opt = fmaf(Lj.x, lS, fmaf(Lo.x, lO, sD));
+      dL = inside ? 0.f : sL + dlO;
+      opt = inside ? Lj.x * Ls : fmaf(Lj.x, lS, fmaf(Lo.x, lO, sD));
     }
   }
   // straight central angle asin(s0 Ls / r_obs) (x <= 0.02: three terms)
-  const float x = s0 * Ls * rcp_fast(robs), x2 = x * x;
+  const float x = s0 * Ls * rc.x, x2 = x * x;
   const float psi_s = x * fmaf(x2, fmaf(x2, 0.075f, 1.0f / 6.0f), 1.0f);
   w.tau = tau;
   w.opt = opt;
@@ -764,7 +805,7 @@ __device__ __forceinline__ bool curved_series(const float4* __restrict__ lay, co
     w.geo = fmaf(0.5f * Ls, fmaf(gx, gx, fmaf(gy, gy, gz * gz)), dL) - dpsi * robs * fmaf(a_t, cps, -a_r * sps);
   }
   w.arrived = 1;
-  curved_arrival(Re, h_obs, Px, Py, Pz, h0, ux, uy, uz, psi_s + dpsi, 0.f, w.ax, w.ay, w.az);
+  curved_arrival(Rf, h_obs, robs, Px, Py, Pz, h0, ux, uy, uz, psi_s + dpsi, 0.f, w.ax, w.ay, w.az);
   return true;
 }
 

@@ -110,13 +110,26 @@ struct KParams {
   int32_t emission;
   double fl_yield[3];
   float fl_lambda[3];
-  // curved Earth
-  double earth_radius;
+  // launch constants derived on the host in the kernels' own precision and order, so
+  // that no lane computes them and none is held in a register across the record loop
+  float inv_lam_span24;      // (inv_lam_min - inv_lam_max) 2^-24
+  float lam_span24;          // (lam_max - lam_min) 2^-24
+  float lam_scale, lam_step; // n_lam / (lam_max - lam_min) and (lam_max - lam_min) / n_lam
+  float half_x, half_y;      // core minus the first cell's edge (GRID) or the first sphere's centre (SPHERES)
+  double half_x64, half_y64, nx64, ny64;  // the same of the grid and its size, FP64 (curved arrival points)
+  // curved Earth: R, 2 R, R + h_obs, lower height of the shell above the observation
+  // shell and the difference of squared radii b_{obs+1}^2 - r_obs^2, 2 R dh; 1 / dh and
+  // the observation shell as the shell walk takes them
+  float Rf, two_Rf, r_obs, h_obs1, d_obs1, two_Rf_dh, inv_dh_walk;
+  int32_t obs_walk;
   int32_t bins_f64;
   // outputs
   void* bins;
   int32_t bins_u64;
-  int32_t lds_hist;                    // grid counts privatised in an LDS window
+  int32_t lds_hist;                    // counts privatised in LDS (a grid window or the sphere array)
+  int32_t hist_words;                  // LDS words of the counts (0 without)
+  int32_t hist_auto;                   // grid: window area in cells, its sides from the shower axis (0: hist_w x hist_h)
+  int32_t sub_shift;                   // the rounds of a tile are shared by 2^sub_shift units of work
   int32_t hist_w, hist_h;              // window size in cells (x, y)
   int32_t hist_x0, hist_y0;            // window origin in cells
   int32_t hist_tw;                     // spheres: leading time bins of each sphere held in LDS too
@@ -160,11 +173,29 @@ TableView table_view(const cphot_table* t);
 const cphot_atmosphere* table_atmosphere(const cphot_table* t);
 double table_h_obs(const cphot_table* t);
 
+// The library's own block size on ground grids: one block per CU (kBig threads).
+constexpr int kBigBlock = 1024;
 hipError_t launch_propagate(const KParams& p, int mode, int block_size, int grid_blocks, size_t lds_hist_bytes,
                             hipStream_t stream);
-// Static LDS bytes of the propagate kernel that `p`, `mode` and `block_size` select.
-// Static LDS bytes of the propagation kernel instance a launch would use (0 if
-// it cannot be queried).
-size_t propagate_static_lds(const KParams& p, int mode, int block_size);
+// The propagation kernel instance that a launch would use: static LDS bytes (0 if it
+// cannot be queried) and the waves per SIMD that its registers allow.
+struct KernelInfo {
+  size_t lds;
+  int waves_per_simd;
+};
+KernelInfo propagate_info(const KParams& p, int block_size);
+// One block size's share of the two (each defined in its own object file).
+template <int BS>
+hipError_t launch_block(const KParams& p, int mode, dim3 grid, size_t lds, hipStream_t s);
+template <int BS>
+KernelInfo info_block(const KParams& p);
+template <> hipError_t launch_block<128>(const KParams&, int, dim3, size_t, hipStream_t);
+template <> hipError_t launch_block<256>(const KParams&, int, dim3, size_t, hipStream_t);
+template <> hipError_t launch_block<512>(const KParams&, int, dim3, size_t, hipStream_t);
+template <> hipError_t launch_block<kBigBlock>(const KParams&, int, dim3, size_t, hipStream_t);
+template <> KernelInfo info_block<128>(const KParams&);
+template <> KernelInfo info_block<256>(const KParams&);
+template <> KernelInfo info_block<512>(const KParams&);
+template <> KernelInfo info_block<kBigBlock>(const KParams&);
 
 }  // namespace cphot

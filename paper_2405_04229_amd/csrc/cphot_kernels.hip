@@ -1,22 +1,25 @@
 // Photon generation and propagation kernels for gfx950.
 //
-// One persistent kernel per (block size, transport, detector, mode). Each block
-// walks tiles of `BS` consecutive segments:
-//   1. coalesced SoA load, one segment per thread; FP64 yield and the
-//      stochastically rounded record count (Sec. 2.2.1); FP32 per-segment
-//      geometry (cone angle, rotation bisector, start point, depth) into LDS;
-//   2. block exclusive scan of the counts -> a flat record index space;
-//   3. every thread takes records j = tid, tid + BS, ... and finds its segment
-//      by binary search over the LDS offsets, then draws the record's Philox
-//      block, builds the photon on the cone (Sec. 4.2), transports it
-//      (Sec. 3.4.1 straight / Sec. 3.4.2 layered), applies absorption
-//      (Sec. 2.3.2) and bins it (LDS-privatised grid histogram or global
-//      atomics); upward photons leave first (Sec. 5.3.4).
+// One kernel per (block size, transport, detector, mode). A wave works on its own
+// tile of 64 consecutive segments, with no block barrier in the loop over tiles:
+//   1. coalesced SoA load, one segment per lane; FP64 yield and the stochastically
+//      rounded record count (Sec. 2.2.1); FP32 per-segment state (cone angle,
+//      rotation bisector, start point, first Philox rounds) into the wave's LDS
+//      slots, sorted by start layer under refracting transports;
+//   2. wave scans of the counts -> flat record numbers, Cherenkov records first,
+//      then fluorescence, each kind in rounds of 64;
+//   3. a round is one record per lane: its slot from a push of the slot starts and
+//      a running maximum over the lanes, then the record's Philox block, the photon
+//      on the cone (Sec. 4.2), its transport (Sec. 3.4.1 straight / Sec. 3.4.2
+//      layered), absorption (Sec. 2.3.2) and its bin (LDS-privatised histogram or
+//      global atomics); upward photons leave first (Sec. 5.3.4).
 // Photons live in registers only; nothing per photon touches HBM except the
-// final bin increment.
+// final bin increment. The waves of a block share the LDS histogram and the tables.
 #include "cphot_device.h"
 #include "cphot_internal.h"
 #include "cphot_mlp.h"
+
+#include <algorithm>
 
 namespace cphot {
 
@@ -184,9 +187,13 @@ __device__ __forceinline__ SegResult segment_setup(const KParams& p, float fx0, 
 struct KConst {
   float4 lin[5];  // (lower bound (m), a, b, 1/c (1/cm)) per Linsley piece
   float4 fl;      // band wavelengths (nm)
+  // hardware reciprocals of launch constants (curved shells): 1 / r_obs, 1 / R^2,
+  // 1 / (b_{obs+1} r_obs)
+  float4 rc;
 };
 
 __device__ __forceinline__ void load_kconst(const KParams& p, KConst& k, int tid) {
+  if (tid == 6) k.rc = make_float4(rcp_fast(p.r_obs), rcp_fast(p.Rf * p.Rf), rcp_fast((p.Rf + p.h_obs1) * p.r_obs), 0.f);
   if (tid < 5) k.lin[tid] = make_float4(p.hb[tid], p.la[tid], p.lb[tid], p.linv_c[tid]);
   if (tid == 5) k.fl = make_float4(p.fl_lambda[0], p.fl_lambda[1], p.fl_lambda[2], 0.f);
 }
@@ -205,8 +212,7 @@ __device__ __forceinline__ float depth_f(const KConst& k, float h) {
 // Squared horizontal distance from (qx, qy) on the observation level to the
 // nearest sphere centre of the shower's array (indices clamped to the array).
 __device__ __forceinline__ float nearest_sphere_d2(const KParams& p, float core_x, float core_y, float qx, float qy) {
-  const float cx0 = core_x - 0.5f * (float)(p.snx - 1) * p.pitch;
-  const float cy0 = core_y - 0.5f * (float)(p.sny - 1) * p.pitch;
+  const float cx0 = core_x - p.half_x, cy0 = core_y - p.half_y;
   const float fi = fminf(fmaxf(rintf((qx - cx0) * p.inv_pitch), 0.f), (float)(p.snx - 1));
   const float fj = fminf(fmaxf(rintf((qy - cy0) * p.inv_pitch), 0.f), (float)(p.sny - 1));
   const float ex = qx - fmaf(fi, p.pitch, cx0), ey = qy - fmaf(fj, p.pitch, cy0);
@@ -276,7 +282,7 @@ __device__ __forceinline__ bool photon_may_hit(const KParams& p, float Px, float
 // Distance from (qx, qy) on the observation level to the shower's ground grid
 // (zero inside it), squared.
 __device__ __forceinline__ float grid_out_d2(const KParams& p, float core_x, float core_y, float qx, float qy) {
-  const float gx0 = core_x - 0.5f * (float)p.nx * p.cell, gy0 = core_y - 0.5f * (float)p.ny * p.cell;
+  const float gx0 = core_x - p.half_x, gy0 = core_y - p.half_y;
   const float gx1 = fmaf((float)p.nx, p.cell, gx0), gy1 = fmaf((float)p.ny, p.cell, gy0);
   const float dx = fmaxf(fmaxf(gx0 - qx, qx - gx1), 0.f), dy = fmaxf(fmaxf(gy0 - qy, qy - gy1), 0.f);
   return fmaf(dx, dx, dy * dy);
@@ -313,7 +319,7 @@ __device__ __forceinline__ bool grid_may_hit(const KParams& p, float Px, float P
 __device__ __forceinline__ bool curved_may_land(const KParams& p, float Px, float Py, float Pz, float ux,
                                                 float uy, float uz, float rq, float h0, float core_x,
                                                 float core_y) {
-  const float Rf = (float)p.earth_radius, r1 = Rf + p.h_obs;
+  const float Rf = p.Rf, r1 = p.r_obs;
   const float irq = rcp_fast(rq);
   const float c0 = -fmaf(ux, Px * irq, fmaf(uy, Py * irq, uz * ((Pz + Rf) * irq)));
   if (!(c0 > 0.f)) return true;
@@ -340,66 +346,145 @@ __device__ __forceinline__ float opt_integral(const KParams& p, float lo, float 
   return p.opt_scale * ((b - a) - (b * b - a * a) / (2.f * t));
 }
 
-// Survival threshold of a record: exp(-tau), times the detector efficiency of
-// its wavelength bin and divided by its segment's reduction factor when set
-// (the detection probability over the probability the record was generated with).
-// Without efficiency the table holds ones, without reduction 1/q is 1: no branches.
-// Under the dispersive spectrum the uniform compared with it is u / p_emit.
-__device__ __forceinline__ float survival_threshold(const KParams& p, const float* __restrict__ s_eff, float tau,
-                                                    int kb, uint32_t inv_q_bits) {
-  return __expf(-tau) * (s_eff[kb] * __uint_as_float(inv_q_bits));
+// Survival threshold of a record, times 2^24 (the records' uniforms stay 24-bit
+// integers in FP32; scaling both sides by a power of two changes no decision):
+// exp(-tau), times the detector efficiency of its wavelength bin and divided by its
+// segment's reduction factor when set (the detection probability over the probability
+// the record was generated with). Without efficiency the table holds 2^24, without
+// reduction 1/q is 1: no branches. Under the dispersive spectrum the uniform compared
+// with it is u / p_emit.
+__device__ __forceinline__ float survival_threshold(const float* __restrict__ s_eff, float tau, int kb,
+                                                    float inv_q) {
+  return __expf(-tau) * (s_eff[kb] * inv_q);
 }
+
+// A launch constant kept in a register across the record loop, in the kernels with
+// registers to spare (kept: 1 scalar, 2 vector for floats). The statement is empty but
+// opaque: without it the register allocator reads the value again from the argument
+// memory in every round, a scalar load and a wait each (ten a round in the telescope
+// kernel, which gains 3 %; batched straight rays 6 %, the network 1.5 %). The curved
+// kernels' scalar registers overflow with it and the lane reads cost more than the loads
+// (inclined 14.9 against 14.5 ms): 0.
+template <int KEPT>
+__device__ __forceinline__ float hold(float v) {
+  if constexpr (KEPT == 2) asm("" : "+v"(v));
+  if constexpr (KEPT == 1) asm("" : "+s"(v));
+  return v;
+}
+template <int KEPT, class T>
+__device__ __forceinline__ T hold(T v) {
+  if constexpr (KEPT != 0) asm("" : "+s"(v));
+  return v;
+}
+
+// The kernel arguments that every record reads (fields as in KParams; each instance keeps
+// those it uses). The others are read where they are used (fresh_params).
+template <int KEPT>
+struct Hot {
+  uint32_t key0, key1;
+  int32_t spectrum, cuts, n_lam, n_layers, obs_layer;
+  float lam_min, inv_lam_min, inv_lam_span24, lam_scale, h_obs, dh, inv_dh;
+  float series_tmax;
+  const float4* moments;
+  int32_t nx, ny, snx, sny, n_t;
+  float inv_cell, pitch, inv_pitch, radius, inv_dt;
+  float Rf, two_Rf, r_obs, h_obs1, d_obs1, two_Rf_dh, inv_dh_walk, shell_rho, shell_tmax;
+  const float* shells;
+  double nx64, ny64, inv_cell64;
+  int32_t hist_tw;
+
+  __device__ __forceinline__ explicit Hot(const KParams& p) {
+#define CPHOT_HOT(f) f = hold<KEPT>(p.f);
+    CPHOT_HOT(key0) CPHOT_HOT(key1) CPHOT_HOT(spectrum) CPHOT_HOT(cuts) CPHOT_HOT(n_lam) CPHOT_HOT(n_layers)
+    CPHOT_HOT(obs_layer) CPHOT_HOT(lam_min) CPHOT_HOT(inv_lam_min) CPHOT_HOT(inv_lam_span24) CPHOT_HOT(lam_scale)
+    CPHOT_HOT(h_obs) CPHOT_HOT(dh) CPHOT_HOT(inv_dh) CPHOT_HOT(series_tmax) CPHOT_HOT(moments) CPHOT_HOT(nx)
+    CPHOT_HOT(ny) CPHOT_HOT(snx) CPHOT_HOT(sny) CPHOT_HOT(n_t) CPHOT_HOT(inv_cell) CPHOT_HOT(pitch)
+    CPHOT_HOT(inv_pitch) CPHOT_HOT(radius) CPHOT_HOT(inv_dt) CPHOT_HOT(Rf) CPHOT_HOT(two_Rf) CPHOT_HOT(r_obs)
+    CPHOT_HOT(h_obs1) CPHOT_HOT(d_obs1) CPHOT_HOT(two_Rf_dh) CPHOT_HOT(inv_dh_walk) CPHOT_HOT(shell_rho)
+    CPHOT_HOT(shell_tmax) CPHOT_HOT(shells) CPHOT_HOT(nx64) CPHOT_HOT(ny64) CPHOT_HOT(inv_cell64) CPHOT_HOT(hist_tw)
+#undef CPHOT_HOT
+  }
+};
 
 template <int T>
 constexpr bool kMlpTransport = (T == CPHOT_TRANSPORT_SURROGATE || T == kTransportCurvedSurrogate);
 
-// A surrogate record outside the network's domain: its transport is redone by the
+// Record states, times 8: a record adds 1 << state to its lane's packed counts.
+constexpr uint32_t kStateUp = 8, kStateAbsorbed = 16, kStateOutside = 24, kStateNotEmitted = 32;
+// A record that the fast path does not serve: its transport is redone by the
 // exact tracer in a separate pass over compacted records.
-constexpr int32_t kStateDeferred = 7;
+constexpr uint32_t kStateDeferred = 56;
 
 struct Photon {
-  int32_t state, bin, tbin, fallback, culled;
+  uint32_t state;
+  int32_t bin, tbin, culled;
   int32_t ix, iy;  // grid cell
   float x, y, z, t, tau, lam, u3, ux, uy, uz;
 };
 
-// One record: emission, transport, absorption, detection. With the surrogate
+// LDS of a block that every record reads.
+struct Tables {
+  const float4* lay;
+  const float2* lam;
+  const MlpImage* img;
+  const KConst* k;
+  const float* eff;   // detector efficiency per wavelength bin, times 2^24
+  uint4* stage;       // this wave's staging of the network's inputs and outputs
+};
+
+// Per-segment state of a record, read from the wave's slot: q0 = start point,
+// cos(theta); q1 = (end - start) 2^-24, sin(theta) (DISPERSIVE: the terms of
+// beta n(lambda) - 1 in place of the angle); q2 = rotation bisector, depth at the
+// start (straight rays) or 1 / q; q3 = Philox words of the segment's id
+// (philox_segment), fluorescence records of band 0 (bit pattern); fl01 = fluorescence
+// records of bands 0 and 1; straight rays: depth change 2^-24 and 1 / q on their own.
+struct SegState {
+  float4 q0, q1, q2, q3;
+  uint32_t fl01;
+  float dX, inv_q;
+};
+
+// The shower that the wave's records belong to: the same in every lane.
+struct ShowerState {
+  int sh;
+  float core_x, core_y, axx, axy, axz;
+  float x0, y0;      // first cell's edge (GRID) or first sphere's centre (SPHERES)
+  double x64, y64;   // first cell's edge in FP64 (curved arrival points)
+};
+
+// One record: emission, transport, absorption, detection. `fl`: fluorescence record,
+// `kk` its index among the segment's records of its kind. With the surrogate
 // transport every lane of the wave must call this together (`valid` marks the
 // lanes that carry a real record); the network is evaluated before any lane
-// leaves.
-template <int TRANSPORT, int DETECTOR, bool NEED_TIME, bool EXT>
-__device__ __forceinline__ void trace(const KParams& p, const float4* __restrict__ s_lay,
-                                      const float2* __restrict__ s_lam, const MlpImage* __restrict__ s_img,
-                                      const KConst* __restrict__ s_k, const float* __restrict__ s_eff,
-                                      uint4* s_stage,
-                                      const float4 q0, const float4 q1, const float4 q2, const float4 q3,
-                                      const float4 q4, const float axz, const uint4 q5, uint32_t k, bool valid,
-                                      Photon& o) {
-  const float sx = q0.x, sy = q0.y, sz = q0.z;
-  const float dx = q1.x, dy = q1.y, dz = q1.z;
-  const float ax = q2.x, ay = q2.y, az = q2.z, X0 = q2.w;
-  const float dX = q3.x;
-  const float core_x = q4.x, core_y = q4.y, axx = q4.z, axy = q4.w;
-  // record k: Cherenkov records first (k < q5.x), then the fluorescence bands
-  float f, lam, u3, ux, uy, uz;
+// leaves. H: the arguments of the common path (Hot, or KParams where few records go).
+template <int TRANSPORT, int DETECTOR, bool NEED_TIME, bool EXT, class K>
+__device__ __forceinline__ void trace(const K& H, const KParams& p, const Tables& T, const SegState& g,
+                                      const ShowerState& S, bool fl, uint32_t kk, bool valid, Photon& o) {
+  const float4* s_lay = T.lay;
+  const float2* s_lam = T.lam;
+  const MlpImage* s_img = T.img;
+  const KConst* s_k = T.k;
+  const float* s_eff = T.eff;
+  uint4* s_stage = T.stage;
+  const float core_x = S.core_x, core_y = S.core_y, axx = S.axx, axy = S.axy, axz = S.axz;
+  float f, lam, u3, ux, uy, uz;  // f and u3 as 24-bit integers
   bool emitted = true;
   float inv_pe = 1.f;
-  if (k < q5.x) {
-    const uint4 w = philox(k, __float_as_uint(q3.y), __float_as_uint(q3.z), TAG_CHERENKOV, p.key0, p.key1);
-    f = u24(w.x);
+  if (!fl) {
+    const uint4 w = philox_record(g.q3, kk, TAG_CHERENKOV, H.key0, H.key1);
+    f = (float)(w.x >> 8);
     float sphi, cphi;
     // the cone azimuth needs sin and cos only to about 2e-5: its error enters the
     // direction times sin(theta) < 0.025; the hardware sine takes revolutions
     const float ua = u24(w.y);
     sphi = __builtin_amdgcn_sinf(ua);
     cphi = __builtin_amdgcn_cosf(ua);
-    const float u2 = u24(w.z);
-    lam = (p.spectrum == CPHOT_SPECTRUM_UNIFORM)
-              ? p.lam_min + (p.lam_max - p.lam_min) * u2
-              : rcp_fast(p.inv_lam_min - u2 * (p.inv_lam_min - p.inv_lam_max));
-    u3 = u24(w.w);
-    float cos_t = q0.w, sin_t = q1.w;
-    if (EXT && p.spectrum == CPHOT_SPECTRUM_DISPERSIVE) {
+    const float u2 = (float)(w.z >> 8);
+    lam = (H.spectrum == CPHOT_SPECTRUM_UNIFORM) ? H.lam_min + p.lam_span24 * u2
+                                                 : rcp_fast(H.inv_lam_min - u2 * H.inv_lam_span24);
+    u3 = (float)(w.w >> 8);
+    float cos_t = g.q0.w, sin_t = g.q1.w;
+    if (EXT && H.spectrum == CPHOT_SPECTRUM_DISPERSIVE) {
       // angle of this wavelength (Eq. 2.5) and the record's emission probability
       // sin^2(theta) / sin^2(theta_max) relative to the cone it was drawn for.
       // g = beta n - 1 is taken as its segment value at lam_min plus the change of
@@ -409,16 +494,17 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
       const float sg = 1000.0f * rcp_fast(lam), sg2 = sg * sg;
       const float dR = (sg2 - p.disp_s2m) *
                        fmaf(p.disp_k1c, rcp_fast(238.0185f - sg2), p.disp_k3c * rcp_fast(57.362f - sg2));
-      const float gm = q1.w;
-      const float g = fmaxf(fmaf(q0.w, dR, gm), 0.f);
-      const float c = rcp_fast(1.0f + g), gg = g * (g + 2.0f);
+      const float gm = g.q1.w;
+      const float gb = fmaxf(fmaf(g.q0.w, dR, gm), 0.f);
+      const float c = rcp_fast(1.0f + gb), gg = gb * (gb + 2.0f);
       const float pe = (gg * (c * c)) * (((1.0f + gm) * (1.0f + gm)) * rcp_fast(gm * (gm + 2.0f)));
-      emitted = u3 < pe;
+      emitted = u3 * kU24 < pe;
       inv_pe = rcp_fast(pe);
       cos_t = c;
       sin_t = sqrt_fast(gg) * c;
     }
     // photon on the cone around (0,0,-1), turned onto the track: u = 2 a (a.p) - p
+    const float ax = g.q2.x, ay = g.q2.y, az = g.q2.z;
     const float plx = cphi * sin_t, ply = sphi * sin_t, plz = -cos_t;
     const float d2 = 2.0f * fmaf(ax, plx, fmaf(ay, ply, az * plz));
     ux = fmaf(d2, ax, -plx);
@@ -426,10 +512,11 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
     uz = fmaf(d2, az, -plz);
   } else {
     // fluorescence (Sec. 4.2.2): isotropic in the lower hemisphere, cos(polar) uniform
-    const uint32_t band = (k < q5.y) ? 0u : ((k < q5.z) ? 1u : 2u);
-    const uint32_t kk = k - (band == 0u ? q5.x : (band == 1u ? q5.y : q5.z));
-    const uint4 w = philox(kk, __float_as_uint(q3.y), __float_as_uint(q3.z), TAG_FLUOR + band, p.key0, p.key1);
-    f = u24(w.x);
+    const uint32_t n0 = __float_as_uint(g.q3.w), n1 = g.fl01;
+    const uint32_t band = (kk < n0) ? 0u : ((kk < n1) ? 1u : 2u);
+    const uint32_t kb = kk - (band == 0u ? 0u : (band == 1u ? n0 : n1));
+    const uint4 w = philox_record(g.q3, kb, TAG_FLUOR + band, H.key0, H.key1);
+    f = (float)(w.x >> 8);
     const float cz = 1.0f - u24(w.y);
     float sphi, cphi;
     sincospif(2.0f * u24(w.z), &sphi, &cphi);
@@ -438,7 +525,7 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
     uy = sz * sphi;
     uz = -cz;
     lam = (&s_k->fl.x)[band];
-    u3 = u24(w.w);
+    u3 = (float)(w.w >> 8);
   }
   o.lam = lam;
   o.u3 = u3;
@@ -446,39 +533,38 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
   if constexpr (EXT) u3 = u3 * inv_pe;
   o.bin = -1;
   o.tbin = -1;
-  o.fallback = 0;
   o.culled = 0;
   o.t = 0.f;
   o.tau = 0.f;
   o.ux = ux;
   o.uy = uy;
   o.uz = uz;
-  const float Px = fmaf(f, dx, sx), Py = fmaf(f, dy, sy), Pz = fmaf(f, dz, sz);
+  const float Px = fmaf(f, g.q1.x, g.q0.x), Py = fmaf(f, g.q1.y, g.q0.y), Pz = fmaf(f, g.q1.z, g.q0.z);
   o.x = Px;
   o.y = Py;
   o.z = Pz;
   if constexpr (EXT && !kMlpTransport<TRANSPORT>) {
     if (!emitted) {  // below the threshold at its wavelength: never emitted
-      o.state = 4;
+      o.state = kStateNotEmitted;
       return;
     }
   }
   int kb = 0;
   if (TRANSPORT != CPHOT_TRANSPORT_STRAIGHT || p.eff) {
-    kb = (int)((lam - p.lam_min) * ((float)p.n_lam / (p.lam_max - p.lam_min)));
-    kb = min(max(kb, 0), p.n_lam - 1);
+    kb = (int)((lam - H.lam_min) * H.lam_scale);
+    kb = min(max(kb, 0), H.n_lam - 1);
   }
   if constexpr (TRANSPORT == CPHOT_TRANSPORT_CURVED || TRANSPORT == kTransportCurvedWalk ||
                 TRANSPORT == kTransportCurvedExact || TRANSPORT == kTransportCurvedSurrogate ||
                 TRANSPORT == kTransportCurvedTable) {
     // height above the sphere R without subtracting R: (x^2 + y^2 + z (2R + z)) / (|P - C| + R)
-    const float Rf = (float)p.earth_radius;
+    const float Rf = H.Rf;
     const float qz = Pz + Rf;
     const float rq = sqrt_fast(fmaf(Px, Px, fmaf(Py, Py, qz * qz)));
-    const float h0 = fmaf(Px, Px, fmaf(Py, Py, Pz * (2.0f * Rf + Pz))) * rcp_fast(rq + Rf);
+    const float h0 = fmaf(Px, Px, fmaf(Py, Py, Pz * (H.two_Rf + Pz))) * rcp_fast(rq + Rf);
     bool cull = false;  // filter level 3: cannot land on the grid
     if constexpr (TRANSPORT != kTransportCurvedExact) {
-      if ((p.cuts & CPHOT_CUT_PHOTON) && uz < 0.f && h0 >= p.h_obs)
+      if ((H.cuts & CPHOT_CUT_PHOTON) && uz < 0.f && h0 >= H.h_obs)
         cull = !curved_may_land(p, Px, Py, Pz, ux, uy, uz, rq, h0, core_x, core_y);
     }
     float ym[kMlpOut] = {0.f, 0.f, 0.f, 0.f};
@@ -489,13 +575,13 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
     if constexpr (TRANSPORT == kTransportCurvedSurrogate) {
       const float irq = rcp_fast(rq);
       c0 = -fmaf(ux, Px * irq, fmaf(uy, Py * irq, uz * (qz * irq)));
-      const bool alive = valid && emitted && (uz < 0.f) && (h0 >= p.h_obs) && !cull;
+      const bool alive = valid && emitted && (uz < 0.f) && (h0 >= H.h_obs) && !cull;
       // the network starts at the start shell's lower boundary R + h_b (the photon is
       // straight inside its homogeneous start shell); a start inside the observation
       // shell is straight all the way (h_b = h_obs, nothing left to correct)
-      j0 = min((int)(h0 * p.inv_dh), p.n_layers - 1);
-      const bool in_obs = j0 <= p.obs_layer;
-      const float h_b = in_obs ? p.h_obs : (float)j0 * p.dh;
+      j0 = min((int)(h0 * H.inv_dh), H.n_layers - 1);
+      const bool in_obs = j0 <= H.obs_layer;
+      const float h_b = in_obs ? H.h_obs : (float)j0 * H.dh;
       const float rc0 = (Rf + h0) * c0;
       const float dJ = (h0 - h_b) * (2.0f * Rf + h0 + h_b);  // r0^2 - r_b^2
       const float gb = fmaf(rc0, rc0, -dJ);                   // r_b^2 cos^2 at the boundary
@@ -503,7 +589,7 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
       const float sgb = sqrt_fast(fmaxf(gb, 0.f));
       leg = reach ? dJ * rcp_fast(rc0 + sgb) : 0.f;
       float xin[kMlpIn] = {h_b, sgb * rcp_fast(Rf + h_b), atan2f(uy, ux),
-                           p.lam_min + ((float)kb + 0.5f) * ((p.lam_max - p.lam_min) / (float)p.n_lam), p.h_obs};
+                           H.lam_min + ((float)kb + 0.5f) * p.lam_step, H.h_obs};
       use_mlp = alive && reach && (in_obs || mlp_in_domain(s_img, xin));
       if (!use_mlp || in_obs) {
 #pragma unroll
@@ -516,20 +602,20 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
         for (int q = 0; q < kMlpOut; ++q) ym[q] = 0.f;
       }
       if (EXT && !emitted) {
-        o.state = 4;
+        o.state = kStateNotEmitted;
         return;
       }
     }
     if (!(uz < 0.f)) {
-      o.state = 1;
+      o.state = kStateUp;
       return;
     }
-    if (h0 < p.h_obs) {
-      o.state = 3;
+    if (h0 < H.h_obs) {
+      o.state = kStateOutside;
       return;
     }
     if (cull) {
-      o.state = 3;
+      o.state = kStateOutside;
       o.culled = 1;
       return;
     }
@@ -539,7 +625,7 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
       c0 = -fmaf(ux, Px * irq, fmaf(uy, Py * irq, uz * (qz * irq)));
       float4 v;
       const float tz = sqrt_fast(fmaxf((1.0f - c0) * (1.0f + c0), 0.f)) * rcp_fast(c0);
-      use_mlp = c0 > 0.f && table_lookup(p.ctab, min((int)(h0 * p.inv_dh), p.n_layers - 1), h0, tz, v);
+      use_mlp = c0 > 0.f && table_lookup(p.ctab, min((int)(h0 * H.inv_dh), H.n_layers - 1), h0, tz, v);
       const float2 sp = s_lam[kb];
       ym[0] = v.x;
       ym[2] = v.y;
@@ -550,9 +636,9 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
       // straight chord to the sphere R + h_obs (cancellation-free root), its
       // central angle, plus the predicted extra ground distance, offset across,
       // optical path excess and log T (the network predicts them per metre of chord)
-      const float r0 = Rf + h0, r1 = Rf + p.h_obs;
+      const float r0 = Rf + h0, r1 = H.r_obs;
       const float s0 = sqrt_fast(fmaxf((1.0f - c0) * (1.0f + c0), 0.f));
-      const float drs = (h0 - p.h_obs) * (r0 + r1);
+      const float drs = (h0 - H.h_obs) * (r0 + r1);
       const float rc = r0 * c0;
       const float s_ch = drs * rcp_fast(rc + sqrt_fast(fmaf(rc, rc, -drs)));
       const float xs = s_ch * s0 * rcp_fast(r1);
@@ -562,7 +648,7 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
       // shell, whose optical depth and n - 1 are added exactly); the table's are absolute
       const float scale = (TRANSPORT == kTransportCurvedTable) ? 1.0f : s_ch - leg;
       const float psi = fmaf(ym[0] * scale, rcp_fast(r1), psi_s);
-      curved_arrival(p.earth_radius, p.h_obs, Px, Py, Pz, h0, ux, uy, uz, psi, ym[1] * scale, cw.ax, cw.ay, cw.az);
+      curved_arrival(Rf, H.h_obs, r1, Px, Py, Pz, h0, ux, uy, uz, psi, ym[1] * scale, cw.ax, cw.ay, cw.az);
       const float4 Lj = s_lay[j0];
       cw.tau = fmaf(fmaf(Lj.z, s_lam[kb].x, Lj.w * s_lam[kb].y), leg, -ym[3] * scale);
       cw.arrived = 1;
@@ -585,20 +671,16 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
       if constexpr (TRANSPORT == CPHOT_TRANSPORT_CURVED || TRANSPORT == kTransportCurvedExact) {
         // closed-form shell sums; rays outside their domain are walked, in a
         // compacted pass (CURVED) or in place (records that are compacted already)
-        if (!curved_series<NEED_TIME>(s_lay, p.shells, s_lam[kb], p.dh, p.n_layers, p.obs_layer, p.h_obs,
-                                      p.earth_radius, p.shell_rho, p.shell_tmax, p.shell_nb_rising != 0, Px, Py, Pz,
-                                      h0, ux, uy, uz, axx, axy, axz, cw)) {
+        if (!curved_series<NEED_TIME>(s_lay, H, p, s_k->rc, s_lam[kb], Px, Py, Pz, rq, h0, ux, uy, uz, axx, axy, axz, cw)) {
           if constexpr (TRANSPORT == CPHOT_TRANSPORT_CURVED) {
             o.state = kStateDeferred;
             return;
           } else {
-            curved_walk<NEED_TIME>(s_lay, s_lam[kb], p.dh, p.n_layers, p.h_obs, p.earth_radius, Px, Py, Pz, h0,
-                                   ux, uy, uz, axx, axy, axz, cw);
+            curved_walk<NEED_TIME>(s_lay, s_lam[kb], p, Px, Py, Pz, h0, ux, uy, uz, axx, axy, axz, cw);
           }
         }
       } else {
-        curved_walk<NEED_TIME>(s_lay, s_lam[kb], p.dh, p.n_layers, p.h_obs, p.earth_radius, Px, Py, Pz, h0, ux, uy,
-                               uz, axx, axy, axz, cw);
+        curved_walk<NEED_TIME>(s_lay, s_lam[kb], p, Px, Py, Pz, h0, ux, uy, uz, axx, axy, axz, cw);
       }
     }
     o.x = (float)cw.ax;
@@ -607,25 +689,23 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
     o.tau = cw.tau;
     if constexpr (NEED_TIME) o.t = (cw.geo + cw.opt) * (1.0f / kCmPerNs);
     if (!cw.arrived) {
-      o.state = 3;
+      o.state = kStateOutside;
       return;
     }
-    if (!(u3 < survival_threshold(p, s_eff, cw.tau, kb, q5.w))) {
-      o.state = 2;
+    if (!(u3 < survival_threshold(s_eff, cw.tau, kb, g.inv_q))) {
+      o.state = kStateAbsorbed;
       return;
     }
     // bins in the tangent plane at the core, in FP64
-    const double gx0 = (double)core_x - 0.5 * (double)p.nx * (double)p.cell;
-    const double gy0 = (double)core_y - 0.5 * (double)p.ny * (double)p.cell;
-    const double fxc = floor((cw.ax - gx0) * p.inv_cell64), fyc = floor((cw.ay - gy0) * p.inv_cell64);
-    if (!(fxc >= 0.0 && fyc >= 0.0 && fxc < (double)p.nx && fyc < (double)p.ny)) {
-      o.state = 3;
+    const double fxc = floor((cw.ax - S.x64) * H.inv_cell64), fyc = floor((cw.ay - S.y64) * H.inv_cell64);
+    if (!(fxc >= 0.0 && fyc >= 0.0 && fxc < H.nx64 && fyc < H.ny64)) {
+      o.state = kStateOutside;
       return;
     }
     o.state = 0;
     o.ix = (int)fxc;
     o.iy = (int)fyc;
-    o.bin = o.iy * p.nx + o.ix;
+    o.bin = o.iy * H.nx + o.ix;
     return;
   } else {
   float ym[kMlpOut] = {0.f, 0.f, 0.f, 0.f};
@@ -633,14 +713,14 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
   float h_b = Pz;   // the network's start: the lower boundary of the start layer (no leg otherwise)
   int j0 = 0;       // start layer
   if constexpr (TRANSPORT == CPHOT_TRANSPORT_SURROGATE) {
-    const bool alive = valid && emitted && (uz < 0.f) && (Pz >= p.h_obs);
+    const bool alive = valid && emitted && (uz < 0.f) && (Pz >= H.h_obs);
     // straight inside the homogeneous start layer; the network takes over at its lower
     // boundary; a start inside the observation layer is straight all the way
-    j0 = min((int)(Pz * p.inv_dh), p.n_layers - 1);
-    const bool in_obs = j0 <= p.obs_layer;
-    h_b = in_obs ? p.h_obs : (float)j0 * p.dh;
+    j0 = min((int)(Pz * H.inv_dh), H.n_layers - 1);
+    const bool in_obs = j0 <= H.obs_layer;
+    h_b = in_obs ? H.h_obs : (float)j0 * H.dh;
     float xin[kMlpIn] = {h_b, -uz, atan2f(uy, ux),
-                         p.lam_min + ((float)kb + 0.5f) * ((p.lam_max - p.lam_min) / (float)p.n_lam), p.h_obs};
+                         H.lam_min + ((float)kb + 0.5f) * p.lam_step, H.h_obs};
     use_mlp = alive && (in_obs || mlp_in_domain(s_img, xin));
     if (!use_mlp || in_obs) {
 #pragma unroll
@@ -653,28 +733,28 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
       for (int q = 0; q < kMlpOut; ++q) ym[q] = 0.f;
     }
     if (EXT && !emitted) {
-      o.state = 4;
+      o.state = kStateNotEmitted;
       return;
     }
   }
   if (!(uz < 0.f)) {
-    o.state = 1;
+    o.state = kStateUp;
     return;
   }
-  if (Pz < p.h_obs) {
-    o.state = 3;
+  if (Pz < H.h_obs) {
+    o.state = kStateOutside;
     return;
   }
   if constexpr (DETECTOR == CPHOT_DETECTOR_SPHERES && !kMlpTransport<TRANSPORT>) {
-    if ((p.cuts & CPHOT_CUT_PHOTON) && !photon_may_hit(p, Px, Py, Pz, ux, uy, uz, core_x, core_y)) {
-      o.state = 3;  // filter level 3: cannot reach a sphere
+    if ((H.cuts & CPHOT_CUT_PHOTON) && !photon_may_hit(p, Px, Py, Pz, ux, uy, uz, core_x, core_y)) {
+      o.state = kStateOutside;  // filter level 3: cannot reach a sphere
       o.culled = 1;
       return;
     }
   }
   if constexpr (DETECTOR == CPHOT_DETECTOR_GRID && !kMlpTransport<TRANSPORT>) {
-    if ((p.cuts & CPHOT_CUT_PHOTON) && !grid_may_hit(p, Px, Py, Pz, ux, uy, uz, core_x, core_y)) {
-      o.state = 3;  // filter level 3: cannot land on the grid
+    if ((H.cuts & CPHOT_CUT_PHOTON) && !grid_may_hit(p, Px, Py, Pz, ux, uy, uz, core_x, core_y)) {
+      o.state = kStateOutside;  // filter level 3: cannot land on the grid
       o.culled = 1;
       return;
     }
@@ -683,7 +763,7 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
     // correction interpolated from the table (Sec. 4.4.1), in the start layer
     float4 v;
     const float tz = sqrtf(fmaf(ux, ux, uy * uy)) / -uz;
-    use_mlp = table_lookup(p.ctab, min((int)(Pz * p.inv_dh), p.n_layers - 1), Pz, tz, v);
+    use_mlp = table_lookup(p.ctab, min((int)(Pz * H.inv_dh), H.n_layers - 1), Pz, tz, v);
     const float2 sp = s_lam[kb];
     ym[0] = v.x;
     ym[2] = v.y;
@@ -700,13 +780,13 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
         return;
       }
       LayerWalk lw;
-      const int j0 = min((int)(Pz * p.inv_dh), p.n_layers - 1);
+      const int j0 = min((int)(Pz * H.inv_dh), H.n_layers - 1);
       // closed-form sums where the series holds, the crossing loop elsewhere
-      if (j0 > p.obs_layer && fmaf(ux, ux, uy * uy) <= p.series_tmax * (uz * uz))
-        layer_series<NEED_TIME>(s_lay, p.moments, s_lam[kb], p.dh, j0, p.obs_layer, Px, Py, Pz, ux, uy, uz, axx,
+      if (j0 > H.obs_layer && fmaf(ux, ux, uy * uy) <= H.series_tmax * (uz * uz))
+        layer_series<NEED_TIME>(s_lay, H.moments, s_lam[kb], H.dh, j0, H.obs_layer, Px, Py, Pz, ux, uy, uz, axx,
                                 axy, axz, lw);
       else
-        layer_walk<NEED_TIME, false>(s_lay, s_lam[kb], p.dh, j0, p.obs_layer, Px, Py, Pz, ux, uy, uz, axx, axy,
+        layer_walk<NEED_TIME, false>(s_lay, s_lam[kb], H.dh, j0, H.obs_layer, Px, Py, Pz, ux, uy, uz, axx, axy,
                                      axz, lw);
       x = lw.x;
       y = lw.y;
@@ -723,14 +803,14 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
       // straight line to the observation level plus the predicted correction:
       // landing (dx, dy), optical path excess e and log T; the delay after the
       // plane front is [l (1 - u.a) + e - (dx a_x + dy a_y)] / c
-      const float s_pl = (p.h_obs - Pz) / uz;
+      const float s_pl = (H.h_obs - Pz) / uz;
       // the predicted offset is along / across the photon's horizontal direction
       const float sh = sqrtf(fmaf(ux, ux, uy * uy));
       const float hx = sh > 0.f ? ux / sh : 1.f, hy = sh > 0.f ? uy / sh : 0.f;
       const float odx = fmaf(ym[0], hx, -ym[1] * hy), ody = fmaf(ym[0], hy, ym[1] * hx);
       x = fmaf(s_pl, ux, Px) + odx;
       y = fmaf(s_pl, uy, Py) + ody;
-      z = p.h_obs;
+      z = H.h_obs;
       vx = ux;
       vy = uy;
       vz = uz;
@@ -744,10 +824,10 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
       const float2 sp = s_lam[kb];
       float tau_s = 0.f, opt_s = 0.f;
       if constexpr (TRANSPORT == CPHOT_TRANSPORT_SURROGATE) {
-        if (j0 > p.obs_layer) {
-          const float4* mr = p.moments + 5 * j0;
-          const float4 Lo = s_lay[p.obs_layer];
-          const float top = (float)(p.obs_layer + 1) * p.dh - p.h_obs;
+        if (j0 > H.obs_layer) {
+          const float4* mr = H.moments + 5 * j0;
+          const float4 Lo = s_lay[H.obs_layer];
+          const float top = (float)(H.obs_layer + 1) * H.dh - H.h_obs;
           tau_s = ic * fmaf(sp.x, mr[2].w, fmaf(sp.y, mr[3].z, fmaf(Lo.z, sp.x, Lo.w * sp.y) * top));
           opt_s = ic * fmaf(Lo.x, top, mr[2].x);
         }
@@ -758,7 +838,7 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
         geo = s_pl * 0.5f * (gx * gx + gy * gy + gz * gz) - (odx * axx + ody * axy);
         opt = fmaf(Lj.x, leg, opt_s + ym[2]);
       }
-      const float4 L = s_lay[p.obs_layer];
+      const float4 L = s_lay[H.obs_layer];
       last_delta = L.x;
       last_ext = fmaf(L.z, sp.x, L.w * sp.y);
     }
@@ -771,31 +851,28 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
     vz = uz;
   }
   // final straight leg: crossing of the observation level
-  const float s_plane = (p.h_obs - z) * rcp_fast(vz);
+  const float s_plane = (H.h_obs - z) * rcp_fast(vz);
   const float Qx = fmaf(s_plane, vx, x), Qy = fmaf(s_plane, vy, y);
   float s_end = s_plane;
   int32_t bin = -1;
   if constexpr (DETECTOR == CPHOT_DETECTOR_GRID) {
-    const float gx0 = core_x - 0.5f * (float)p.nx * p.cell;
-    const float gy0 = core_y - 0.5f * (float)p.ny * p.cell;
-    const float fxc = floorf((Qx - gx0) * p.inv_cell), fyc = floorf((Qy - gy0) * p.inv_cell);
-    if (fxc >= 0.f && fyc >= 0.f && fxc < (float)p.nx && fyc < (float)p.ny) {
+    const float fxc = floorf((Qx - S.x0) * H.inv_cell), fyc = floorf((Qy - S.y0) * H.inv_cell);
+    if (fxc >= 0.f && fyc >= 0.f && fxc < (float)H.nx && fyc < (float)H.ny) {
       o.ix = (int)fxc;
       o.iy = (int)fyc;
-      bin = o.iy * p.nx + o.ix;
+      bin = o.iy * H.nx + o.ix;
     }
   } else {
-    const float cx0 = core_x - 0.5f * (float)(p.snx - 1) * p.pitch;
-    const float cy0 = core_y - 0.5f * (float)(p.sny - 1) * p.pitch;
-    const float fi = floorf((Qx - cx0) * p.inv_pitch + 0.5f), fj = floorf((Qy - cy0) * p.inv_pitch + 0.5f);
-    if (fi >= 0.f && fj >= 0.f && fi < (float)p.snx && fj < (float)p.sny) {
-      const float qx = Qx - (cx0 + fi * p.pitch), qy = Qy - (cy0 + fj * p.pitch);
+    const float cx0 = S.x0, cy0 = S.y0;
+    const float fi = floorf((Qx - cx0) * H.inv_pitch + 0.5f), fj = floorf((Qy - cy0) * H.inv_pitch + 0.5f);
+    if (fi >= 0.f && fj >= 0.f && fi < (float)H.snx && fj < (float)H.sny) {
+      const float qx = Qx - (cx0 + fi * H.pitch), qy = Qy - (cy0 + fj * H.pitch);
       const float b = qx * vx + qy * vy;  // q_z = 0 on the observation level
-      const float cc = qx * qx + qy * qy - p.radius * p.radius;
+      const float cc = qx * qx + qy * qy - H.radius * H.radius;
       const float disc = b * b - cc;
       if (disc >= 0.f) {
         s_end = s_plane + (-b - sqrt_fast(disc));
-        bin = (int)fj * p.snx + (int)fi;
+        bin = (int)fj * H.snx + (int)fi;
       }
     }
   }
@@ -810,7 +887,7 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
   } else {
     // straight line in a planar atmosphere: closed forms over the height span
     const float inv_uz = -1.0f / vz;  // 1/|u_z|
-    const float Xe = fmaf(f, dX, X0);
+    const float Xe = fmaf(f, g.dX, g.q2.w);
     float X_end = p.X_obs;
     if constexpr (DETECTOR == CPHOT_DETECTOR_SPHERES) {
       if (p.profile == CPHOT_PROFILE_LINSLEY5) X_end = depth_f(*s_k, ez);
@@ -835,20 +912,20 @@ __device__ __forceinline__ void trace(const KParams& p, const float4* __restrict
   o.z = ez;
   o.tau = tau;
   if constexpr (NEED_TIME) o.t = (geo + opt) * (1.0f / kCmPerNs);
-  if (!(u3 < survival_threshold(p, s_eff, tau, kb, q5.w))) {
-    o.state = 2;
+  if (!(u3 < survival_threshold(s_eff, tau, kb, g.inv_q))) {
+    o.state = kStateAbsorbed;
     return;
   }
   if (bin < 0) {
-    o.state = 3;
+    o.state = kStateOutside;
     return;
   }
   o.state = 0;
   o.bin = bin;
   if constexpr (DETECTOR == CPHOT_DETECTOR_SPHERES) {
-    if (p.n_t > 0) {
-      const float tb = floorf(o.t * p.inv_dt);
-      o.tbin = tb < 0.f ? 0 : (tb >= (float)p.n_t ? p.n_t : (int)tb);
+    if (H.n_t > 0) {
+      const float tb = floorf(o.t * H.inv_dt);
+      o.tbin = tb < 0.f ? 0 : (tb >= (float)H.n_t ? H.n_t : (int)tb);
     }
   }
   }
@@ -867,103 +944,146 @@ __device__ __forceinline__ int shower_of(const KParams& p, int64_t i) {
   return lo;
 }
 
+// The kernel's arguments, read anew: the address passes through a statement that the
+// compiler cannot see through, so that values used once per record are loaded (scalar
+// cache) where they are used. Hoisted out of the record loop they overflow the scalar
+// registers by over a hundred, and each use reads them back with a lane read.
+__device__ __forceinline__ const KParams& fresh_params() {
+  auto q = __builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(q));
+  return *(const KParams*)q;
+}
+
+// A value that is the same in every lane, in a scalar register.
+__device__ __forceinline__ float uniform(float v) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(v)));
+}
+
+__device__ __forceinline__ double uniform(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Adds w photons to element b of the global bins.
+__device__ __forceinline__ void add_bin(const KParams& p, int64_t b, uint32_t w) {
+  if (p.bins_f64) atomicAdd(reinterpret_cast<double*>(p.bins) + b, (double)(float)w);
+  else if (p.bins_u64) atomicAdd(reinterpret_cast<unsigned long long*>(p.bins) + b, (unsigned long long)w);
+  else atomicAdd(reinterpret_cast<uint32_t*>(p.bins) + b, w);
+}
+
+// A block's LDS window: the rectangle of grid cells (or the sphere array) it holds.
+struct Window {
+  int w, h, x0, y0;
+};
+
+// The window of a shower's grid. The launch gives the rectangle, or only its area
+// (hist_auto): then the sides are in the ratio of the extents of a round spot, cast along
+// the shower axis, on the ground (1 + (axis_x / axis_z)^2 and the same in y, squared), and
+// the rectangle is centred on the grid. Photons of a shower inclined by 60 degrees that
+// miss a square of the same area cost a device atomic each.
+__device__ __forceinline__ Window shower_window(const KParams& p, int sh) {
+  Window w = {p.hist_w, p.hist_h, p.hist_x0, p.hist_y0};
+  if (p.hist_auto) {
+    const double* g = p.geom + 5 * (int64_t)sh;
+    const float ex = (float)(g[2] / g[4]), ey = (float)(g[3] / g[4]);
+    const float area = (float)p.hist_auto;
+    const float side = sqrtf(area * sqrtf(fmaf(ex, ex, 1.0f) / fmaf(ey, ey, 1.0f)));
+    // an axis along the ground (or no number) gives the whole width
+    w.w = side < (float)p.nx ? max((int)side, 1) : p.nx;
+    w.h = min(p.hist_auto / w.w, p.ny);
+    if (w.h == p.ny) w.w = min(p.hist_auto / w.h, p.nx);
+    w.w = __builtin_amdgcn_readfirstlane(w.w);
+    w.h = __builtin_amdgcn_readfirstlane(w.h);
+    w.x0 = (p.nx - w.w) / 2;
+    w.y0 = (p.ny - w.h) / 2;
+  }
+  return w;
+}
+
 // Adds the LDS window of shower `sh` (record counts) to the global bins with
-// the bunch weight, and clears it. Called by the whole block. The window is a
-// rectangle of grid cells, or the whole sphere array.
+// the bunch weight, and clears it. Called by the whole block. A wave takes whole
+// rows, so that its atomics fall on consecutive cells.
 template <int BS, int DETECTOR>
-__device__ void flush_window(const KParams& p, uint32_t* s_hist, int sh) {
-  const int n = p.hist_w * p.hist_h;
+__device__ void flush_window(const KParams& p, uint32_t* s_hist, const Window& win, int sh) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int row = DETECTOR == CPHOT_DETECTOR_GRID ? p.nx : p.snx;
   const int64_t base = (int64_t)sh * row * (DETECTOR == CPHOT_DETECTOR_GRID ? p.ny : p.sny);
-  for (int b = threadIdx.x; b < n; b += BS) {
-    const uint32_t v = s_hist[b];
-    if (v) {
-      const int ly = b / p.hist_w, lx = b - ly * p.hist_w;
-      const int64_t gb = base + (int64_t)(p.hist_y0 + ly) * row + (p.hist_x0 + lx);
-      const unsigned long long w = (unsigned long long)v * (unsigned long long)p.bunch;
-      if (p.bins_f64) atomicAdd(reinterpret_cast<double*>(p.bins) + gb, (double)w);
-      else if (p.bins_u64) atomicAdd(reinterpret_cast<unsigned long long*>(p.bins) + gb, w);
-      else atomicAdd(reinterpret_cast<uint32_t*>(p.bins) + gb, (uint32_t)w);
-      s_hist[b] = 0u;
+  for (int ly = wave; ly < win.h; ly += BS / 64) {
+    for (int lx = lane; lx < win.w; lx += 64) {
+      const uint32_t v = s_hist[ly * win.w + lx];
+      if (v) {
+        const int64_t gb = base + (int64_t)(win.y0 + ly) * row + (win.x0 + lx);
+        const unsigned long long w = (unsigned long long)v * (unsigned long long)p.bunch;
+        if (p.bins_f64) atomicAdd(reinterpret_cast<double*>(p.bins) + gb, (double)w);
+        else if (p.bins_u64) atomicAdd(reinterpret_cast<unsigned long long*>(p.bins) + gb, w);
+        else atomicAdd(reinterpret_cast<uint32_t*>(p.bins) + gb, (uint32_t)w);
+        s_hist[ly * win.w + lx] = 0u;
+      }
     }
   }
   if constexpr (DETECTOR == CPHOT_DETECTOR_SPHERES) {
     // leading time bins of every sphere, after the sphere counts
-    const int nt = n * p.hist_tw;
-    uint32_t* s_t = s_hist + n;
-    for (int b = threadIdx.x; b < nt; b += BS) {
-      const uint32_t v = s_t[b];
-      if (v) {
-        const int sph = b / p.hist_tw, tb = b - sph * p.hist_tw;
-        atomicAdd(p.thist + (base + sph) * (p.n_t + 1) + tb, v * (uint32_t)p.bunch);
-        s_t[b] = 0u;
+    const int n = win.w * win.h;
+    for (int sph = wave; sph < n; sph += BS / 64) {
+      for (int tb = lane; tb < p.hist_tw; tb += 64) {
+        uint32_t* s_t = s_hist + n + sph * p.hist_tw + tb;
+        const uint32_t v = *s_t;
+        if (v) {
+          atomicAdd(p.thist + (base + sph) * (p.n_t + 1) + tb, v * (uint32_t)p.bunch);
+          *s_t = 0u;
+        }
       }
     }
   }
 }
 
-// Waves per SIMD the register allocation must leave room for. The curved-table
-// kernel sits two registers above the three-wave limit without the bound; the
-// curved walk runs 15 % faster at four waves with a few spilled registers than
-// at three without.
-template <int T>
-constexpr int kMinWavesPerSimd =
-    (T == kTransportCurvedTable || T == CPHOT_TRANSPORT_CURVED) ? 3
-    : (T == kTransportCurvedWalk || T == CPHOT_TRANSPORT_LAYERED ||
-       T == CPHOT_TRANSPORT_STRAIGHT || T == CPHOT_TRANSPORT_TABLE)
-        ? 4
-                                                                                                                     : 1;
+// Waves per SIMD the register allocation must leave room for: four (128 registers) for
+// the exact tracers, whose time falls with the waves up to there (inclined step with a
+// window that catches its photons: 26.6, 17.7 and 14.4 ms at two, three and four); the
+// network's activations allow two, three in the block of 768 with a few values of the
+// tile set-up in scratch.
+template <int BS, int T>
+constexpr int kMinWaves = !kMlpTransport<T> ? 4 : BS == 768 ? 3 : 2;
 
 // EXT: Poisson record counts and the dispersive spectrum (its per-record angle and
 // emission decision), compiled only into the kernels that run them: as runtime
 // branches their registers cost the default path spills and about a tenth of its
 // time.
 template <int BS, int TRANSPORT, int DETECTOR, int MODE, bool EXT>
-__global__ __launch_bounds__(BS, kMinWavesPerSimd<TRANSPORT>) void k_propagate(KParams p) {
+__global__ __launch_bounds__(BS, (kMinWaves<BS, TRANSPORT>)) void k_propagate(KParams p) {
   constexpr bool kTime = (DETECTOR == CPHOT_DETECTOR_SPHERES) || (MODE == MODE_RECORDS);
   constexpr bool kLayers = (TRANSPORT != CPHOT_TRANSPORT_STRAIGHT);
   constexpr bool kMlp = (TRANSPORT == CPHOT_TRANSPORT_SURROGATE || TRANSPORT == kTransportCurvedSurrogate);
   // transports that defer some records to the exact tracer (compaction queue)
   constexpr bool kDefer = kMlp || TRANSPORT == CPHOT_TRANSPORT_TABLE || TRANSPORT == kTransportCurvedTable ||
                           TRANSPORT == CPHOT_TRANSPORT_CURVED;
-  constexpr bool kSort = kLayers && (MODE != MODE_COUNTS);
-  // ground-grid kernels number a tile's records Cherenkov first, then fluorescence,
-  // so that a wave holds one kind of record (one emission branch, one Philox call)
-  // except at the single boundary; straight rays cost too little per record for the
-  // second scan and its LDS to pay
-  constexpr bool kSplit =
-      (DETECTOR == CPHOT_DETECTOR_GRID) && (MODE != MODE_COUNTS) && (TRANSPORT != CPHOT_TRANSPORT_STRAIGHT);
+  constexpr bool kRecords = MODE == MODE_RECORDS;
+  constexpr int kWaves = BS / 64;
   // exact transport behind a surrogate: records outside the network's domain
   constexpr int kExact =
       (TRANSPORT == CPHOT_TRANSPORT_SURROGATE || TRANSPORT == CPHOT_TRANSPORT_TABLE)       ? CPHOT_TRANSPORT_LAYERED
       : (TRANSPORT == kTransportCurvedSurrogate || TRANSPORT == kTransportCurvedTable) ? kTransportCurvedExact
       : (TRANSPORT == CPHOT_TRANSPORT_CURVED)                                               ? kTransportCurvedWalk
                                                                                             : TRANSPORT;
-  // per-segment state for the record loop, one slot per segment of the tile:
-  // q0 = start point, cos(theta); q1 = end - start, sin(theta) (DISPERSIVE: the
-  // terms of beta n(lambda) - 1 in place of the angle); q2 = rotation
-  // bisector, depth at the start; q3 = depth change, id low, id high, shower
-  // (bit patterns); q4 = core x, core y, axis x, axis y; axz = axis z
-  __shared__ float4 s_q0[BS], s_q1[BS], s_q2[BS], s_q3[BS], s_q4[BS];
-  __shared__ float s_axz[BS];
-  __shared__ uint4 s_q5[BS];  // record boundaries: Cherenkov, + band 0, + band 1
-  __shared__ uint32_t s_off[BS + 1];
-  __shared__ uint32_t s_offf[kSplit ? BS + 1 : 1];  // fluorescence record offsets
-  __shared__ uint32_t s_wave[2 * (BS / 64)];
-  __shared__ uint32_t s_src[kSort ? BS : 1];          // tile-local segment index of each slot
-  __shared__ uint32_t s_bucket[kSort ? kMaxLayers + 1 : 1];
+  // per-segment state for the record loop (SegState), 64 slots per wave
+  __shared__ float4 s_q0[BS], s_q1[BS], s_q2[BS], s_q3[BS];
+  __shared__ uint32_t s_fl01[BS];
+  __shared__ float2 s_dx[kLayers ? 1 : BS];
+  // record dumps: the segment's global id, its first record's place, its Cherenkov records
+  __shared__ ulonglong2 s_rec[kRecords ? BS : 1];
+  __shared__ uint32_t s_nch[kRecords ? BS : 1];
   __shared__ float4 s_lay[kLayers ? kMaxLayers : 1];
   __shared__ float2 s_lam[kLayers ? kMaxLambdaBins : 1];
   __shared__ uint4 s_imgw[kMlp ? sizeof(MlpImage) / 16 : 1];
-  // compaction queues of deferred records (slot, k), one ring of 128 entries per
-  // wave: at most 64 enter per round and the wave drains 64 at a time once it
-  // holds that many, so a ring never holds more than 127
-  __shared__ uint16_t s_qlo[kDefer ? 2 * BS : 1];
-  __shared__ uint32_t s_qk[kDefer ? 2 * BS : 1];
+  // compaction queue of deferred records (slot + 64 kind + 128 index), 64 entries per
+  // wave: the wave traces what it holds when a round's records would not fit
+  __shared__ uint32_t s_queue[kDefer ? BS : 1];
   __shared__ uint4 s_mlpx[kMlp ? BS : 1];  // per-wave staging of the network's inputs and outputs
   __shared__ KConst s_k;
-  __shared__ float s_eff[kMaxLambdaBins];  // detector efficiency per wavelength bin
-  const MlpImage* s_img = reinterpret_cast<const MlpImage*>(s_imgw);
+  __shared__ float s_eff[kMaxLambdaBins];  // detector efficiency per wavelength bin, times 2^24
+  __shared__ unsigned long long s_cnt[CPHOT_NCOUNTERS];
   // Optional LDS window of the grid, or the whole sphere array (record counts of
   // one shower at a time). With it each block walks a contiguous range of tiles,
   // so the window changes shower only a few times per block; records outside the
@@ -971,12 +1091,10 @@ __global__ __launch_bounds__(BS, kMinWavesPerSimd<TRANSPORT>) void k_propagate(K
   // directly. Without it every hit is a device atomic, and hits on one sphere
   // serialise on its cache line.
   extern __shared__ uint32_t s_hist[];
-  __shared__ int s_win_sh, s_tile_sh;
-  __shared__ uint32_t s_since;  // records since the last flush (keeps LDS counts below 2^32)
-  const int n_hist = (MODE == MODE_PROPAGATE && p.lds_hist)
-                         ? p.hist_w * p.hist_h * (DETECTOR == CPHOT_DETECTOR_SPHERES ? 1 + p.hist_tw : 1)
-                         : 0;
-  const int tid = threadIdx.x;
+  __shared__ unsigned long long s_since;  // records counted in the window since the last flush
+  __shared__ uint32_t s_next;             // next tile of the block's run, from its first
+  const int n_hist = MODE == MODE_PROPAGATE ? p.hist_words : 0;
+  const int tid = threadIdx.x, lane = tid & 63, wbase = tid & ~63;
 
   if constexpr (kLayers) {
     for (int i = tid; i < p.n_layers; i += BS) s_lay[i] = p.layers[i];
@@ -987,326 +1105,450 @@ __global__ __launch_bounds__(BS, kMinWavesPerSimd<TRANSPORT>) void k_propagate(K
     for (int i = tid; i < (int)(sizeof(MlpImage) / 16); i += BS) s_imgw[i] = src[i];
   }
   load_kconst(p, s_k, tid);
-  for (int i = tid; i < kMaxLambdaBins; i += BS) s_eff[i] = (p.eff && i < p.n_lam) ? (float)p.eff[i] : 1.0f;
+  for (int i = tid; i < kMaxLambdaBins; i += BS)
+    s_eff[i] = ((p.eff && i < p.n_lam) ? (float)p.eff[i] : 1.0f) * 16777216.0f;
   for (int i = tid; i < n_hist; i += BS) s_hist[i] = 0u;
-  if (tid == 0) {
-    s_win_sh = -1;
-    s_since = 0u;
-  }
+  if (tid < CPHOT_NCOUNTERS) s_cnt[tid] = 0ull;
+  if (tid == 0) s_since = 0ull;
   __syncthreads();
+  const Tables T = {s_lay, s_lam, reinterpret_cast<const MlpImage*>(s_imgw), &s_k, s_eff,
+                    s_mlpx + (kMlp ? wbase : 0)};
 
-  uint32_t c_in = 0, c_skip = 0, c_below = 0, c_gen = 0, c_up = 0, c_abs = 0, c_out = 0, c_bin = 0, c_fb = 0;
-  uint32_t c_fl = 0, c_cut1 = 0, c_cut3 = 0;
-  const int64_t n_tiles = (p.n + BS - 1) / BS;
-  int64_t t_first = blockIdx.x, t_end = n_tiles, t_step = gridDim.x;
+  constexpr int kKept = (TRANSPORT == CPHOT_TRANSPORT_STRAIGHT || TRANSPORT == CPHOT_TRANSPORT_LAYERED ||
+                         TRANSPORT == CPHOT_TRANSPORT_TABLE)
+                            ? 2
+                            : kMlp ? 1 : 0;
+  const Hot<kKept> H(p);
+
+  // Units of work: a tile of 64 segments, or with sub_shift one of the 2^sub_shift equal
+  // shares of its record rounds. With an LDS histogram the block walks a contiguous range
+  // of them, one run per shower; its waves draw units from the run as they finish.
+  // Without, the waves of the grid take units in turn.
+  const int sub = p.sub_shift;
+  const int64_t n_units = ((p.n + 63) >> 6) << sub;
+  int64_t u_first = 0, u_end = n_units;
   if (n_hist) {
-    t_first = (int64_t)blockIdx.x * n_tiles / gridDim.x;
-    t_end = ((int64_t)blockIdx.x + 1) * n_tiles / gridDim.x;
-    t_step = 1;
+    u_first = (int64_t)blockIdx.x * n_units / gridDim.x;
+    u_end = ((int64_t)blockIdx.x + 1) * n_units / gridDim.x;
   }
-  for (int64_t tile = t_first; tile < t_end; tile += t_step) {
-    const int64_t i = tile * BS + tid;
+  int win_sh = -1;
+  Window win = {0, 0, 0, 0};
+  for (int64_t run = u_first, run_end; run < u_end; run = run_end) {
+    run_end = u_end;
     if (n_hist) {
-      if (tid == 0) s_tile_sh = shower_of(p, tile * BS);
-      __syncthreads();
-      // per tile at most BS << 20 records: flushing at 2^31 keeps counts below 2^32
-      if (s_tile_sh != s_win_sh || s_since >= (1u << 31)) {
-        if (s_win_sh >= 0) flush_window<BS, DETECTOR>(p, s_hist, s_win_sh);
+      const KParams& p = fresh_params();
+      const int sh = shower_of(p, (run >> sub) << 6);
+      if (sh + 1 < p.n_showers) run_end = min(u_end, ((p.offsets[sh + 1] + 63) >> 6) << sub);
+      if (run != u_first) {
         __syncthreads();
-        if (tid == 0) {
-          s_win_sh = s_tile_sh;
-          s_since = 0u;
-        }
+        flush_window<BS, DETECTOR>(p, s_hist, win, win_sh);
         __syncthreads();
       }
+      win_sh = sh;
+      win = shower_window(p, sh);
+      if (tid == 0) {
+        s_next = 0u;
+        s_since = 0ull;
+      }
+      __syncthreads();
     }
-    uint32_t nrec = 0;
-    float4 q0 = make_float4(0.f, 0.f, 0.f, 0.f), q1 = q0, q2 = q0, q3 = q0, q4 = q0;
-    float axz = 0.f;
-    uint4 q5 = make_uint4(0u, 0u, 0u, 0u);
-    int key = kMaxLayers;  // segments without records sort last
-    if (i < p.n) {
-      const float fx0 = p.x0[i], fy0 = p.y0[i], fz0 = p.z0[i], fx1 = p.x1[i], fy1 = p.y1[i], fz1 = p.z1[i];
-      const uint64_t id = p.first_id + (uint64_t)i * p.id_stride;
-      SegResult r =
-          segment_setup<EXT>(p, fx0, fy0, fz0, fx1, fy1, fz1, p.beta[i], p.charge[i], p.dedx ? p.dedx[i] : 0.0f, id);
-      if constexpr (MODE == MODE_PROPAGATE && DETECTOR == CPHOT_DETECTOR_SPHERES && !kMlpTransport<TRANSPORT>) {
-        if ((p.cuts & CPHOT_CUT_TRACK) && r.n > 0) {
-          const double* gc = p.geom + 5 * shower_of(p, i);
-          if (!track_may_hit(p, fx0, fy0, fz0, fx1, fy1, fz1, r.cos_t, r.sin_t, (float)gc[0], (float)gc[1])) {
-            c_cut1 += (uint32_t)r.n;  // filter level 1: no photon of the cone can reach a sphere
-            r.n = 0;
+    for (int64_t turn = (int64_t)blockIdx.x * kWaves + (tid >> 6);; turn += (int64_t)gridDim.x * kWaves) {
+      int64_t unit = turn;
+      if (n_hist) {
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&s_next, 1u);
+        unit = run + (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+      }
+      if (unit >= run_end) break;
+      const int64_t tile = unit >> sub;
+      const uint32_t share = (uint32_t)unit & ((1u << sub) - 1u);
+      const KParams& p = fresh_params();
+      // ---- 1. the tile's segments, one per lane
+      const int64_t i = (tile << 6) + lane;
+      uint32_t n_ch = 0, n_fl = 0;
+      float4 q0 = make_float4(0.f, 0.f, 0.f, 0.f), q1 = q0, q2 = q0, q3 = q0;
+      uint2 fl_n = make_uint2(0u, 0u);
+      float inv_q = 1.f;
+      uint32_t key = kMaxLayers;  // segments without records sort last
+      int status = 0;
+      uint32_t cut1 = 0;
+      uint32_t sh_of = 0;
+      float dXs = 0.f;
+      uint64_t id = 0;
+      if (i < p.n) {
+        const float fx0 = p.x0[i], fy0 = p.y0[i], fz0 = p.z0[i], fx1 = p.x1[i], fy1 = p.y1[i], fz1 = p.z1[i];
+        id = p.first_id + (uint64_t)i * p.id_stride;
+        SegResult r = segment_setup<EXT>(p, fx0, fy0, fz0, fx1, fy1, fz1, p.beta[i], p.charge[i],
+                                         p.dedx ? p.dedx[i] : 0.0f, id);
+        if constexpr (MODE == MODE_PROPAGATE && DETECTOR == CPHOT_DETECTOR_SPHERES && !kMlpTransport<TRANSPORT>) {
+          if ((p.cuts & CPHOT_CUT_TRACK) && r.n > 0) {
+            const double* gc = p.geom + 5 * shower_of(p, i);
+            if (!track_may_hit(p, fx0, fy0, fz0, fx1, fy1, fz1, r.cos_t, r.sin_t, (float)gc[0], (float)gc[1])) {
+              cut1 = (uint32_t)r.n;  // filter level 1: no photon of the cone can reach a sphere
+              r.n = 0;
+            }
+          }
+        }
+        status = r.status;
+        n_ch = (uint32_t)r.n;
+        fl_n = make_uint2((uint32_t)r.nf[0], (uint32_t)(r.nf[0] + r.nf[1]));
+        inv_q = r.inv_q;
+        n_fl = (uint32_t)(r.nf[0] + r.nf[1] + r.nf[2]);
+        if (n_ch + n_fl) {
+          sh_of = (uint32_t)shower_of(p, i);
+          float X0 = 0.f;
+          if (!kLayers && p.profile == CPHOT_PROFILE_LINSLEY5) {
+            X0 = depth_f(s_k, fz0);
+            dXs = (depth_f(s_k, fz1) - X0) * kU24;
+          }
+          const bool disp = EXT && p.spectrum == CPHOT_SPECTRUM_DISPERSIVE;
+          const uint3 ph = philox_segment((uint32_t)id, (uint32_t)(id >> 32), p.key0, p.key1);
+          q0 = make_float4(fx0, fy0, fz0, disp ? r.disp_a : r.cos_t);
+          q1 = make_float4((fx1 - fx0) * kU24, (fy1 - fy0) * kU24, (fz1 - fz0) * kU24, disp ? r.disp_gm : r.sin_t);
+          q2 = make_float4(r.a0, r.a1, r.a2, kLayers ? inv_q : X0);
+          q3 = make_float4(__uint_as_float(ph.x), __uint_as_float(ph.y), __uint_as_float(ph.z),
+                           __uint_as_float(fl_n.x));
+          if constexpr (kLayers) key = (uint32_t)min(max((int)(0.5f * (fz0 + fz1) * p.inv_dh), 0), p.n_layers - 1);
+        }
+      }
+      // slot of this segment: sorted by start layer under layered transport, so that
+      // the lanes of a wave read the same table rows and cross similar numbers of layers
+      const int slot = wbase + (kLayers ? (int)wave_rank<8>(key) : lane);
+      wave_fence();  // the previous tile's slots have been read
+      s_q0[slot] = q0;
+      s_q1[slot] = q1;
+      s_q2[slot] = q2;
+      s_q3[slot] = q3;
+      s_fl01[slot] = fl_n.y;
+      if constexpr (!kLayers) s_dx[slot] = make_float2(dXs, inv_q);
+      if constexpr (kRecords) {
+        s_rec[slot] = make_ulonglong2(id, i < p.n ? (unsigned long long)p.rec_off[i] : 0ull);
+        s_nch[slot] = n_ch;
+      }
+      // ---- 2. record numbers: lane L holds slot L's counts and, below, offsets
+      if constexpr (kLayers) {
+        const int to = (slot - wbase) << 2;
+        n_ch = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)n_ch);
+        n_fl = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)n_fl);
+        if (p.n_showers > 1) sh_of = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)sh_of);
+      }
+      if constexpr (MODE == MODE_PROPAGATE) {
+        if (share == 0) {
+          const uint32_t v_in = (uint32_t)__popcll(__ballot(i < p.n)), v_skip = (uint32_t)__popcll(__ballot(status == 2)),
+                         v_below = (uint32_t)__popcll(__ballot(status == 1));
+          const uint32_t v_fl = (p.emission & CPHOT_EMIT_FLUORESCENCE) ? wave_total(n_fl) : 0u;
+          const uint32_t v_cut = (p.cuts & CPHOT_CUT_TRACK) ? wave_total(cut1) : 0u;
+          if (lane == 0) {
+            atomicAdd(&s_cnt[CPHOT_C_SEGMENTS_IN], (unsigned long long)v_in);
+            if (v_skip) atomicAdd(&s_cnt[CPHOT_C_SEGMENTS_SKIPPED], (unsigned long long)v_skip);
+            if (v_below) atomicAdd(&s_cnt[CPHOT_C_SEGMENTS_BELOW_THRESHOLD], (unsigned long long)v_below);
+            if (v_fl) atomicAdd(&s_cnt[CPHOT_C_RECORDS_FLUORESCENCE], (unsigned long long)v_fl);
+            if (v_cut) atomicAdd(&s_cnt[CPHOT_C_RECORDS_CULLED_TRACK], (unsigned long long)v_cut);
           }
         }
       }
-      c_in += 1;
-      c_skip += r.status == 2;
-      c_below += r.status == 1;
-      q5 = make_uint4((uint32_t)r.n, (uint32_t)(r.n + r.nf[0]), (uint32_t)(r.n + r.nf[0] + r.nf[1]),
-                      __float_as_uint(r.inv_q));
-      nrec = q5.z + (uint32_t)r.nf[2];
-      c_fl += nrec - (uint32_t)r.n;
-      if constexpr (MODE == MODE_COUNTS) {
-        p.counts[i] = (int32_t)nrec;
-        if (p.expected) p.expected[i] = r.status == 0 ? r.mu : 0.0;
-      } else if (nrec) {
-        const int sh = shower_of(p, i);
-        float X0 = 0.f, dXs = 0.f;
-        if (TRANSPORT == CPHOT_TRANSPORT_STRAIGHT && p.profile == CPHOT_PROFILE_LINSLEY5) {
-          X0 = depth_f(s_k, fz0);
-          dXs = depth_f(s_k, fz1) - X0;
-        }
-        const double* g = p.geom + 5 * sh;
-        const bool disp = EXT && p.spectrum == CPHOT_SPECTRUM_DISPERSIVE;
-        q0 = make_float4(fx0, fy0, fz0, disp ? r.disp_a : r.cos_t);
-        q1 = make_float4(fx1 - fx0, fy1 - fy0, fz1 - fz0, disp ? r.disp_gm : r.sin_t);
-        q2 = make_float4(r.a0, r.a1, r.a2, X0);
-        q3 = make_float4(dXs, __uint_as_float((uint32_t)id), __uint_as_float((uint32_t)(id >> 32)),
-                         __uint_as_float((uint32_t)sh));
-        q4 = make_float4((float)g[0], (float)g[1], (float)g[2], (float)g[3]);
-        axz = (float)g[4];
-        if constexpr (kSort) key = min(max((int)(0.5f * (fz0 + fz1) * p.inv_dh), 0), p.n_layers - 1);
-      }
-    }
-    if constexpr (MODE == MODE_COUNTS) continue;
-    // slot of this segment in the tile: sorted by start layer under layered
-    // transport, so that the lanes of a wave cross similar numbers of layers
-    int slot = tid;
-    if constexpr (kSort) {
-      for (int b = tid; b <= kMaxLayers; b += BS) s_bucket[b] = 0u;
-      __syncthreads();
-      const uint32_t rank = atomicAdd(&s_bucket[key], 1u);
-      __syncthreads();
-      if (tid < 64) {  // exclusive scan of the bucket sizes by one wave
-        uint32_t carry = 0;
-        for (int base = 0; base <= kMaxLayers; base += 64) {
-          const int b = base + tid;
-          const uint32_t v = b <= kMaxLayers ? s_bucket[b] : 0u;
-          uint32_t x = v;
-#pragma unroll
-          for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t y = __shfl_up(x, d, 64);
-            if (tid >= d) x += y;
+      wave_fence();  // the slots are complete
+      // A tile's records are numbered shower by shower (nearly always one), so that the
+      // shower is the same in every lane and takes no slot memory.
+      const uint32_t all_ch = n_ch, all_fl = n_fl;
+      for (uint64_t todo = __ballot((all_ch | all_fl) != 0u); todo;) {
+        ShowerState S;
+        S.sh = 0;
+        if (p.n_showers > 1) S.sh = __builtin_amdgcn_readlane((int)sh_of, (int)__builtin_ctzll(todo));
+        const bool mine = p.n_showers <= 1 || (int)sh_of == S.sh;
+        todo &= ~__ballot(mine);
+        n_ch = mine ? all_ch : 0u;
+        n_fl = mine ? all_fl : 0u;
+        {
+          const double* g = p.geom + 5 * (int64_t)S.sh;
+          S.core_x = uniform((float)g[0]);
+          S.core_y = uniform((float)g[1]);
+          S.x0 = uniform(S.core_x - p.half_x);
+          S.y0 = uniform(S.core_y - p.half_y);
+          S.x64 = uniform((double)S.core_x - p.half_x64);
+          S.y64 = uniform((double)S.core_y - p.half_y64);
+          S.axx = S.axy = S.axz = 0.f;
+          if constexpr (kTime) {
+            S.axx = uniform((float)g[2]);
+            S.axy = uniform((float)g[3]);
+            S.axz = uniform((float)g[4]);
           }
-          if (b <= kMaxLayers) s_bucket[b] = carry + x - v;
-          carry += __shfl(x, 63, 64);
         }
-      }
-      __syncthreads();
-      slot = (int)(s_bucket[key] + rank);
-      s_src[slot] = (uint32_t)tid;
-    }
-    s_q0[slot] = q0;
-    s_q1[slot] = q1;
-    s_q2[slot] = q2;
-    s_q3[slot] = q3;
-    s_q4[slot] = q4;
-    s_axz[slot] = axz;
-    s_q5[slot] = q5;
-    s_off[slot] = kSplit ? q5.x : nrec;
-    if constexpr (kSplit) s_offf[slot] = nrec - q5.x;
-    __syncthreads();
-    uint32_t total, total_c = 0;
-    if constexpr (kSplit) {
-      uint32_t total_f;
-      const uint2 excl = block_exclusive_scan2<BS>(s_off[tid], s_offf[tid], s_wave, total_c, total_f);
-      __syncthreads();
-      s_off[tid] = excl.x;
-      s_offf[tid] = excl.y;
-      total = total_c + total_f;
-    } else {
-      const uint32_t mine = s_off[tid];
-      const uint32_t excl = block_exclusive_scan<BS>(mine, s_wave, total);
-      __syncthreads();
-      s_off[tid] = excl;
-    }
-    if (tid == BS - 1) s_since += total;
-    __syncthreads();
-    // with the surrogate every lane of a wave runs each round (the tail lanes
-    // repeat the last record and discard it); otherwise lanes stop at `total`
-    const uint32_t rounds_end = kDefer ? ((total + BS - 1) / BS) * BS : total;
-    // one record: a parity dump, or counters and bins
-    auto consume = [&](const Photon& ph, int lo, uint32_t k, const float4& r3) {
-      if constexpr (MODE == MODE_RECORDS) {
-        const uint32_t src = kSort ? s_src[lo] : (uint32_t)lo;
-        const int64_t slot_out = p.rec_off[tile * BS + src] + (int64_t)k;
-        if (slot_out < p.rec_cap) {
-          cphot_photon_record rr;
-          rr.seg = ((uint64_t)__float_as_uint(r3.z) << 32) | __float_as_uint(r3.y);
-          rr.k = k;
-          rr.state = ph.state;
-          rr.bin = ph.bin;
-          rr.tbin = ph.tbin;
-          rr.x = ph.x; rr.y = ph.y; rr.z = ph.z;
-          rr.t = ph.t; rr.tau = ph.tau; rr.lambda = ph.lam;
-          rr.dx = ph.ux; rr.dy = ph.uy; rr.dz = ph.uz;
-          rr.u_abs = ph.u3;
-          p.rec[slot_out] = rr;
+        const uint32_t end_ch = wave_scan_add(n_ch), end_fl = wave_scan_add(n_fl);
+        const uint32_t total_ch = (uint32_t)__builtin_amdgcn_readlane((int)end_ch, 63);
+        const uint32_t total_fl = (uint32_t)__builtin_amdgcn_readlane((int)end_fl, 63);
+        // per wave at most 64 << 22 records in a tile; window counts stay below 2^32
+        // because a tile that could take them beyond goes to the global bins directly
+        bool use_win = n_hist != 0 && S.sh == win_sh;
+        if (use_win) {
+          unsigned long long was = 0;
+          if (lane == 0) was = atomicAdd(&s_since, (unsigned long long)total_ch + total_fl);
+          use_win = !__builtin_amdgcn_readfirstlane((int)(was + total_ch + total_fl > (1ull << 31)));
         }
-      } else {
-        c_gen += 1;
-        c_fb += ph.fallback;
-        c_cut3 += ph.culled;
-        c_up += ph.state == 1;
-        c_abs += ph.state == 2;
-        c_out += ph.state == 3;
-        if (ph.state == 0) {
-          c_bin += 1;
-          const uint32_t sh = __float_as_uint(r3.w);
-          if constexpr (DETECTOR == CPHOT_DETECTOR_GRID) {
-            const int lx = ph.ix - p.hist_x0, ly = ph.iy - p.hist_y0;
-            if (n_hist && (int)sh == s_win_sh && (unsigned)lx < (unsigned)p.hist_w &&
-                (unsigned)ly < (unsigned)p.hist_h) {
-              atomicAdd(&s_hist[ly * p.hist_w + lx], 1u);
-            } else {
-              const int64_t gb = (int64_t)sh * p.nx * p.ny + ph.bin;
-              if (p.bins_f64) atomicAdd(reinterpret_cast<double*>(p.bins) + gb, (double)(float)p.bunch);
-              else if (p.bins_u64) atomicAdd(reinterpret_cast<unsigned long long*>(p.bins) + gb, (unsigned long long)p.bunch);
-              else atomicAdd(reinterpret_cast<uint32_t*>(p.bins) + gb, p.bunch);
+        // ---- 3. rounds of 64 records, Cherenkov rounds first (at most 2^23, 2^8 shares)
+        const uint32_t rounds_ch = (total_ch + 63) >> 6, rounds = rounds_ch + ((total_fl + 63) >> 6);
+        const uint32_t r_first = rounds * share >> sub, r_end = rounds * (share + 1) >> sub;
+        uint32_t done = 0, culled = 0, fallback = 0, not_emitted = 0;  // the same in every lane
+        uint32_t packed = 0, in_packed = 0;  // this lane's counts of states 0..3, 8 bits each; additions since the last unpacking
+        auto unpack = [&]() {
+          const uint32_t a = wave_total(packed & 0x00ff00ffu), b = wave_total((packed >> 8) & 0x00ff00ffu);
+          if (lane == 0) {
+            atomicAdd(&s_cnt[CPHOT_C_RECORDS_BINNED], (unsigned long long)(a & 0xffffu));
+            atomicAdd(&s_cnt[CPHOT_C_RECORDS_ABSORBED], (unsigned long long)(a >> 16));
+            atomicAdd(&s_cnt[CPHOT_C_RECORDS_UPWARD], (unsigned long long)(b & 0xffffu));
+            atomicAdd(&s_cnt[CPHOT_C_RECORDS_OUTSIDE], (unsigned long long)(b >> 16));
+          }
+          packed = 0;
+          in_packed = 0;
+        };
+        auto load_slot = [&](int s, SegState& g) {
+          g.q0 = s_q0[s];
+          g.q1 = s_q1[s];
+          g.q2 = s_q2[s];
+          g.q3 = s_q3[s];
+          g.fl01 = s_fl01[s];
+          g.dX = 0.f;
+          g.inv_q = g.q2.w;
+          if constexpr (!kLayers) {
+            const float2 x = s_dx[s];
+            g.dX = x.x;
+            g.inv_q = x.y;
+          }
+        };
+        // one record (its kind, and its index within the segment's records of the kind): a
+        // parity dump, or counters and bins
+        auto consume = [&](const KParams& p, const Photon& ph, int s, bool fl, uint32_t kk) {
+          if constexpr (kRecords) {
+            const ulonglong2 rec = s_rec[s];
+            const uint32_t k = fl ? kk + s_nch[s] : kk;
+            const int64_t at = (int64_t)rec.y + (int64_t)k;
+            if (at < p.rec_cap) {
+              cphot_photon_record rr;
+              rr.seg = rec.x;
+              rr.k = k;
+              rr.state = (int32_t)(ph.state >> 3);
+              rr.bin = ph.bin;
+              rr.tbin = ph.tbin;
+              rr.x = ph.x; rr.y = ph.y; rr.z = ph.z;
+              rr.t = ph.t; rr.tau = ph.tau; rr.lambda = ph.lam;
+              rr.dx = ph.ux; rr.dy = ph.uy; rr.dz = ph.uz;
+              rr.u_abs = ph.u3 * kU24;
+              p.rec[at] = rr;
             }
           } else {
-            const int64_t nsph = (int64_t)p.snx * p.sny;
-            const int64_t gb = (int64_t)sh * nsph + ph.bin;
-            const bool win = n_hist && (int)sh == s_win_sh;
-            if (win) {
-              atomicAdd(&s_hist[ph.bin], 1u);
-            } else {
-              if (p.bins_f64) atomicAdd(reinterpret_cast<double*>(p.bins) + gb, (double)(float)p.bunch);
-              else if (p.bins_u64) atomicAdd(reinterpret_cast<unsigned long long*>(p.bins) + gb, (unsigned long long)p.bunch);
-              else atomicAdd(reinterpret_cast<uint32_t*>(p.bins) + gb, p.bunch);
+            if (!EXT || ph.state != kStateNotEmitted) packed += 1u << ph.state;
+            if (ph.state == 0u) {
+              if constexpr (DETECTOR == CPHOT_DETECTOR_GRID) {
+                const int lx = ph.ix - win.x0, ly = ph.iy - win.y0;
+                if (use_win && (unsigned)lx < (unsigned)win.w && (unsigned)ly < (unsigned)win.h)
+                  atomicAdd(&s_hist[ly * win.w + lx], 1u);
+                else
+                  add_bin(p, (int64_t)S.sh * p.nx * p.ny + ph.bin, p.bunch);
+              } else {
+                const int64_t nsph = (int64_t)H.snx * H.sny;
+                const int64_t gb = (int64_t)S.sh * nsph + ph.bin;
+                if (use_win) atomicAdd(&s_hist[ph.bin], 1u);
+                else add_bin(p, gb, p.bunch);
+                if (H.n_t > 0) {
+                  if (use_win && ph.tbin < H.hist_tw) atomicAdd(&s_hist[nsph + ph.bin * H.hist_tw + ph.tbin], 1u);
+                  else atomicAdd(p.thist + gb * (H.n_t + 1) + ph.tbin, p.bunch);
+                }
+              }
             }
-            if (p.n_t > 0) {
-              if (win && ph.tbin < p.hist_tw) atomicAdd(&s_hist[nsph + ph.bin * p.hist_tw + ph.tbin], 1u);
-              else atomicAdd(p.thist + gb * (p.n_t + 1) + ph.tbin, p.bunch);
+          }
+        };
+        uint32_t q_len = 0;  // this wave's queue of deferred records (the same in every lane)
+        uint32_t* queue = s_queue + (kDefer ? wbase : 0);
+        for (uint32_t r = r_first; r < r_end; ++r) {
+          const KParams& pr = fresh_params();
+          const bool fl = r >= rounds_ch;
+          const uint32_t j0 = (fl ? r - rounds_ch : r) << 6, total = fl ? total_fl : total_ch;
+          const uint32_t cnt = fl ? n_fl : n_ch, off = (fl ? end_fl : end_ch) - cnt;
+          // slot of record j0 + lane: the last slot that starts at or before it. The slots
+          // that start inside the round push their number to the lane they start at (only
+          // slots with records: no two at one lane); lane 0 gets the slot j0 lies in.
+          const uint32_t cur = (uint32_t)__popcll(__ballot(off <= j0)) - 1u;
+          const uint32_t d = off - j0;
+          const bool starts = cnt != 0u && d - 1u < 63u;
+          uint32_t at = (uint32_t)__builtin_amdgcn_ds_permute(starts ? (int)(d << 2) : 0, lane);
+          at = wave_scan_max(lane == 0 ? cur : at);
+          const uint32_t kk = j0 + (uint32_t)lane - (uint32_t)__builtin_amdgcn_ds_bpermute((int)(at << 2), (int)off);
+          const bool valid = j0 + (uint32_t)lane < total;
+          const int s = wbase + (int)at;
+          done += min(total - j0, 64u);
+          Photon ph;
+          ph.state = kStateNotEmitted;
+          ph.culled = 0;
+          if (kMlp || valid) {
+            SegState g;
+            load_slot(s, g);
+            trace<TRANSPORT, DETECTOR, kTime, EXT>(H, pr, T, g, S, fl, kk, valid, ph);
+            if (valid && (!kDefer || ph.state != kStateDeferred)) consume(pr, ph, s, fl, kk);
+          }
+          if constexpr (MODE == MODE_PROPAGATE) {
+            if (H.cuts & CPHOT_CUT_PHOTON) culled += (uint32_t)__popcll(__ballot(valid && ph.culled));
+            if (EXT) not_emitted += (uint32_t)__popcll(__ballot(valid && ph.state == kStateNotEmitted));
+            if (++in_packed == 255u) unpack();
+          }
+          if constexpr (kDefer) {
+            // wave-level compaction: deferred records take consecutive entries of this wave's
+            // queue (ballot and prefix count of the lanes below); the wave traces the queue
+            // exactly when they would not fit, and after the last round
+            const bool push = valid && ph.state == kStateDeferred;
+            const uint64_t mask = __ballot(push);
+            const uint32_t n_push = (uint32_t)__popcll(mask);
+            const bool last = r + 1u == r_end;
+#pragma unroll 1
+            for (int pass = 0; pass < 2; ++pass) {
+              if (pass == 0 ? q_len + n_push > 64u : last && q_len > 0u) {
+                wave_fence();  // the queue's entries are complete
+                if ((uint32_t)lane < q_len) {
+                  const KParams& pq = fresh_params();
+                  const uint32_t e = queue[lane];
+                  const int qs = wbase + (int)(e & 63u);
+                  const bool qfl = (e & 64u) != 0u;
+                  const uint32_t qk = e >> 7;
+                  SegState g;
+                  load_slot(qs, g);
+                  Photon pe;
+                  trace<kExact, DETECTOR, kTime, EXT>(pq, pq, T, g, S, qfl, qk, true, pe);
+                  consume(pq, pe, qs, qfl, qk);
+                }
+                wave_fence();  // every lane has read its entry before the queue takes new ones
+                fallback += q_len;
+                q_len = 0;
+                if constexpr (MODE == MODE_PROPAGATE) {
+                  if (++in_packed == 255u) unpack();
+                }
+              }
+              if (pass == 0) {
+                if (push) {
+                  const uint32_t below =
+                      __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                  queue[q_len + below] = at | (fl ? 64u : 0u) | (kk << 7);
+                }
+                q_len += n_push;
+              }
             }
           }
         }
-      }
-    };
-    uint32_t q_head = 0, q_len = 0;  // this wave's ring of deferred records (same in every lane)
-    for (uint32_t base = 0; base + tid < rounds_end; base += BS) {
-      const uint32_t jr = base + tid;
-      const bool valid = jr < total;
-      const uint32_t j = valid ? jr : total - 1;
-      // largest slot lo in [0, BS) with offset <= j (offsets never decrease); with
-      // the split numbering, records from total_c on are the fluorescence records
-      const bool fl = kSplit && j >= total_c;
-      const uint32_t* offs = fl ? s_offf : s_off;
-      const uint32_t jj = fl ? j - total_c : j;
-      int lo = 0;
-#pragma unroll
-      for (int step = BS / 2; step >= 1; step >>= 1) lo += (offs[lo + step] <= jj) ? step : 0;
-      const uint32_t k = jj - offs[lo] + (fl ? s_q5[lo].x : 0u);
-      Photon ph;
-      const float4 r3 = s_q3[lo];
-      trace<TRANSPORT, DETECTOR, kTime, EXT>(p, s_lay, s_lam, s_img, &s_k, s_eff, s_mlpx + (kMlp ? (tid & ~63) : 0), s_q0[lo],
-                                        s_q1[lo], s_q2[lo], r3, s_q4[lo], s_axz[lo], s_q5[lo], k, valid, ph);
-      if constexpr (kDefer) {
-        // wave-level compaction: deferred records take consecutive entries of this
-        // wave's ring (ballot and prefix count of the lanes below); the wave traces
-        // them exactly, 64 at a time, with no block barrier
-        const bool push = valid && ph.state == kStateDeferred;
-        const uint64_t mask = __ballot(push);
-        const uint32_t lane = (uint32_t)(tid & 63);
-        uint16_t* q_lo = s_qlo + 2 * (tid & ~63);
-        uint32_t* q_k = s_qk + 2 * (tid & ~63);
-        if (push) {
-          const uint32_t pos = (q_head + q_len + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull))) & 127u;
-          q_lo[pos] = (uint16_t)lo;
-          q_k[pos] = k;
-        }
-        q_len += (uint32_t)__popcll(mask);
-        if (valid && !push) consume(ph, lo, k, r3);
-        const bool last = base + BS >= rounds_end;
-        while (q_len >= 64u || (last && q_len > 0u)) {
-          // the ring's entries written by other lanes of this wave are complete
-          // (the fences order the LDS accesses; no other wave touches this ring)
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-          __builtin_amdgcn_wave_barrier();
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-          const uint32_t take = min(q_len, 64u);
-          if (lane < take) {
-            const uint32_t e = (q_head + lane) & 127u;
-            const int qlo = q_lo[e];
-            const uint32_t qk = q_k[e];
-            const float4 q3 = s_q3[qlo];
-            Photon pe;
-            trace<kExact, DETECTOR, kTime, EXT>(p, s_lay, s_lam, s_img, &s_k, s_eff, s_mlpx, s_q0[qlo], s_q1[qlo], s_q2[qlo], q3,
-                                           s_q4[qlo], s_axz[qlo], s_q5[qlo], qk, true, pe);
-            pe.fallback = 1;
-            consume(pe, qlo, qk, q3);
+        if constexpr (MODE == MODE_PROPAGATE) {
+          unpack();
+          if (lane == 0) {
+            if (done) atomicAdd(&s_cnt[CPHOT_C_RECORDS_GENERATED], (unsigned long long)done);
+            if (fallback) atomicAdd(&s_cnt[CPHOT_C_SURROGATE_FALLBACK], (unsigned long long)fallback);
+            if (culled) atomicAdd(&s_cnt[CPHOT_C_RECORDS_CULLED_PHOTON], (unsigned long long)culled);
+            if (not_emitted) atomicAdd(&s_cnt[CPHOT_C_RECORDS_NOT_EMITTED], (unsigned long long)not_emitted);
           }
-          // every lane has read its entry before the ring takes new ones
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-          __builtin_amdgcn_wave_barrier();
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-          q_head = (q_head + take) & 127u;
-          q_len -= take;
         }
-      } else {
-        if (valid) consume(ph, lo, k, r3);
       }
     }
-    __syncthreads();
   }
   if constexpr (MODE == MODE_PROPAGATE) {
-    if (n_hist) {
-      __syncthreads();
-      if (s_win_sh >= 0) flush_window<BS, DETECTOR>(p, s_hist, s_win_sh);
-    }
-    if (p.counters) {
-      // block-level reduction: one global atomic per counter per block (same-address
-      // device atomics serialise, so their number must stay small)
-      __shared__ uint32_t s_cnt[13];
-      if (tid < 13) s_cnt[tid] = 0u;
-      __syncthreads();
-      // every consumed record has exactly one final state; the records not emitted
-      // (state 4) are the rest, so they need no accumulator of their own
-      const uint32_t c_ne = c_gen - c_up - c_abs - c_out - c_bin;  // modulo 2^32: exact over the block
-      const uint32_t v[13] = {c_in,  c_skip, c_below, c_gen, c_up,   c_abs, c_out,
-                              c_bin, c_fb,   c_fl,    c_cut1, c_cut3, c_ne};
-#pragma unroll
-      for (int q = 0; q < 13; ++q) {
-        const uint32_t sw = wave_sum(v[q]);
-        if ((tid & 63) == 0 && sw) atomicAdd(&s_cnt[q], sw);
-      }
-      __syncthreads();
-      if (tid < 8 && s_cnt[tid]) atomicAdd(p.counters + tid, (unsigned long long)s_cnt[tid]);
-      if (tid == 8 && s_cnt[7]) atomicAdd(p.counters + CPHOT_C_PHOTONS_BINNED, (unsigned long long)s_cnt[7] * p.bunch);
-      if (tid == 9 && s_cnt[8]) atomicAdd(p.counters + CPHOT_C_SURROGATE_FALLBACK, (unsigned long long)s_cnt[8]);
-      if (tid == 10 && s_cnt[9]) atomicAdd(p.counters + CPHOT_C_RECORDS_FLUORESCENCE, (unsigned long long)s_cnt[9]);
-      if (tid == 11 && s_cnt[10]) atomicAdd(p.counters + CPHOT_C_RECORDS_CULLED_TRACK, (unsigned long long)s_cnt[10]);
-      if (tid == 12 && s_cnt[11]) atomicAdd(p.counters + CPHOT_C_RECORDS_CULLED_PHOTON, (unsigned long long)s_cnt[11]);
-      if (tid == 13 && s_cnt[12]) atomicAdd(p.counters + CPHOT_C_RECORDS_NOT_EMITTED, (unsigned long long)s_cnt[12]);
+    __syncthreads();
+    if (win_sh >= 0) flush_window<BS, DETECTOR>(p, s_hist, win, win_sh);
+    if (p.counters && tid < CPHOT_NCOUNTERS) {
+      // one global atomic per counter and block (same-address device atomics
+      // serialise, so their number must stay small)
+      const unsigned long long v =
+          tid == CPHOT_C_PHOTONS_BINNED ? s_cnt[CPHOT_C_RECORDS_BINNED] * p.bunch : s_cnt[tid];
+      if (v) atomicAdd(p.counters + tid, v);
     }
   }
 }
+
+#if CPHOT_BLOCK == 256
+// Records and expected records per segment.
+template <bool EXT>
+__global__ __launch_bounds__(256) void k_counts(KParams p) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < p.n; i += (int64_t)gridDim.x * 256) {
+    const uint64_t id = p.first_id + (uint64_t)i * p.id_stride;
+    const SegResult r = segment_setup<EXT>(p, p.x0[i], p.y0[i], p.z0[i], p.x1[i], p.y1[i], p.z1[i], p.beta[i],
+                                           p.charge[i], p.dedx ? p.dedx[i] : 0.0f, id);
+    p.counts[i] = r.n + r.nf[0] + r.nf[1] + r.nf[2];
+    if (p.expected) p.expected[i] = r.status == 0 ? r.mu : 0.0;
+  }
+}
+#endif
 
 namespace {
 
 template <int BS, int T, int D, int M, bool EXT>
-hipError_t launch_one(const KParams& p, int grid, size_t lds, hipStream_t s) {
-  hipLaunchKernelGGL((k_propagate<BS, T, D, M, EXT>), dim3(grid), dim3(BS), lds, s, p);
+hipError_t launch_one(const KParams& p, dim3 grid, size_t lds, hipStream_t s) {
+  hipLaunchKernelGGL((k_propagate<BS, T, D, M, EXT>), grid, dim3(BS), lds, s, p);
   return hipGetLastError();
 }
 
-template <int BS, int T, int D, int M>
-hipError_t launch_ext(const KParams& p, int grid, size_t lds, hipStream_t s) {
+#if CPHOT_BLOCK != 1024
+template <int BS, int T, int D>
+hipError_t launch_mode(const KParams& p, int mode, dim3 grid, size_t lds, hipStream_t s) {
   const bool ext = p.poisson || p.spectrum == CPHOT_SPECTRUM_DISPERSIVE;
-  return ext ? launch_one<BS, T, D, M, true>(p, grid, lds, s) : launch_one<BS, T, D, M, false>(p, grid, lds, s);
+  if (mode == MODE_PROPAGATE)
+    return ext ? launch_one<BS, T, D, MODE_PROPAGATE, true>(p, grid, lds, s)
+               : launch_one<BS, T, D, MODE_PROPAGATE, false>(p, grid, lds, s);
+  return ext ? launch_one<BS, T, D, MODE_RECORDS, true>(p, grid, lds, s)
+             : launch_one<BS, T, D, MODE_RECORDS, false>(p, grid, lds, s);
 }
+#endif
 
 template <int BS, int T, int D>
-hipError_t launch_mode(const KParams& p, int mode, int grid, size_t lds, hipStream_t s) {
-  switch (mode) {
-    case MODE_PROPAGATE: return launch_ext<BS, T, D, MODE_PROPAGATE>(p, grid, lds, s);
-    case MODE_COUNTS: return launch_ext<BS, T, D, MODE_COUNTS>(p, grid, lds, s);
-    default: return launch_ext<BS, T, D, MODE_RECORDS>(p, grid, lds, s);
-  }
+KernelInfo info_one() {
+  hipFuncAttributes a;
+  // the EXT kernels declare the same static LDS and run at the same waves per SIMD
+  if (hipFuncGetAttributes(&a, reinterpret_cast<const void*>(&k_propagate<BS, T, D, MODE_PROPAGATE, false>)) != hipSuccess)
+    return {0, 1};
+  const int regs = (std::max(a.numRegs, 1) + 7) / 8 * 8;  // allocated by eights from 512 per lane and SIMD
+  return {a.sharedSizeBytes, std::min(8, 512 / regs)};
 }
 
-template <int BS>
-hipError_t launch_bs(const KParams& p, int mode, int grid, size_t lds, hipStream_t s) {
+}  // namespace
+
+// Each block size is compiled by itself (CPHOT_BLOCK), so that they build side by side.
+// The large size serves the library's own choice on ground grids: 1024 threads, or 768
+// for the network kernels, whose registers allow three waves per SIMD.
+#if CPHOT_BLOCK == 1024
+template <int T>
+constexpr int kBig = kMlpTransport<T> ? 768 : 1024;
+
+template <>
+hipError_t launch_block<1024>(const KParams& p, int mode, dim3 grid, size_t lds, hipStream_t s) {
+  (void)mode;
+  const bool ext = p.poisson || p.spectrum == CPHOT_SPECTRUM_DISPERSIVE;
+#define CPHOT_BIG(T) \
+  case T: \
+    return ext ? launch_one<kBig<T>, T, 0, MODE_PROPAGATE, true>(p, grid, lds, s) \
+               : launch_one<kBig<T>, T, 0, MODE_PROPAGATE, false>(p, grid, lds, s);
+  switch (p.transport) {
+    CPHOT_BIG(CPHOT_TRANSPORT_STRAIGHT)
+    CPHOT_BIG(CPHOT_TRANSPORT_LAYERED)
+    CPHOT_BIG(CPHOT_TRANSPORT_SURROGATE)
+    CPHOT_BIG(CPHOT_TRANSPORT_CURVED)
+    CPHOT_BIG(CPHOT_TRANSPORT_TABLE)
+    CPHOT_BIG(kTransportCurvedWalk)
+    CPHOT_BIG(kTransportCurvedTable)
+    CPHOT_BIG(kTransportCurvedSurrogate)
+    default: return hipErrorInvalidValue;
+  }
+#undef CPHOT_BIG
+}
+
+template <>
+KernelInfo info_block<1024>(const KParams& p) {
+  switch (p.transport) {
+    case CPHOT_TRANSPORT_STRAIGHT: return info_one<1024, CPHOT_TRANSPORT_STRAIGHT, 0>();
+    case CPHOT_TRANSPORT_LAYERED: return info_one<1024, CPHOT_TRANSPORT_LAYERED, 0>();
+    case CPHOT_TRANSPORT_SURROGATE: return info_one<768, CPHOT_TRANSPORT_SURROGATE, 0>();
+    case CPHOT_TRANSPORT_CURVED: return info_one<1024, CPHOT_TRANSPORT_CURVED, 0>();
+    case CPHOT_TRANSPORT_TABLE: return info_one<1024, CPHOT_TRANSPORT_TABLE, 0>();
+    case kTransportCurvedWalk: return info_one<1024, kTransportCurvedWalk, 0>();
+    case kTransportCurvedTable: return info_one<1024, kTransportCurvedTable, 0>();
+    default: return info_one<768, kTransportCurvedSurrogate, 0>();
+  }
+}
+#else
+template <>
+hipError_t launch_block<CPHOT_BLOCK>(const KParams& p, int mode, dim3 grid, size_t lds, hipStream_t s) {
+  constexpr int BS = CPHOT_BLOCK;
   const bool g = p.detector == CPHOT_DETECTOR_GRID;
   switch (p.transport) {
     case CPHOT_TRANSPORT_STRAIGHT: return g ? launch_mode<BS, 0, 0>(p, mode, grid, lds, s) : launch_mode<BS, 0, 1>(p, mode, grid, lds, s);
@@ -1320,55 +1562,50 @@ hipError_t launch_bs(const KParams& p, int mode, int grid, size_t lds, hipStream
   }
 }
 
-template <int BS, int T, int D, int M>
-size_t static_lds_one() {
-  hipFuncAttributes a;
-  // the EXT kernels declare the same static LDS
-  if (hipFuncGetAttributes(&a, reinterpret_cast<const void*>(&k_propagate<BS, T, D, M, false>)) != hipSuccess) return 0;
-  return a.sharedSizeBytes;
-}
-
-template <int BS, int T, int D>
-size_t static_lds_mode(int mode) {
-  switch (mode) {
-    case MODE_PROPAGATE: return static_lds_one<BS, T, D, MODE_PROPAGATE>();
-    case MODE_COUNTS: return static_lds_one<BS, T, D, MODE_COUNTS>();
-    default: return static_lds_one<BS, T, D, MODE_RECORDS>();
-  }
-}
-
-template <int BS>
-size_t static_lds_bs(const KParams& p, int mode) {
+template <>
+KernelInfo info_block<CPHOT_BLOCK>(const KParams& p) {
+  constexpr int BS = CPHOT_BLOCK;
   const bool g = p.detector == CPHOT_DETECTOR_GRID;
   switch (p.transport) {
-    case CPHOT_TRANSPORT_STRAIGHT: return g ? static_lds_mode<BS, 0, 0>(mode) : static_lds_mode<BS, 0, 1>(mode);
-    case CPHOT_TRANSPORT_LAYERED: return g ? static_lds_mode<BS, 1, 0>(mode) : static_lds_mode<BS, 1, 1>(mode);
-    case CPHOT_TRANSPORT_SURROGATE: return g ? static_lds_mode<BS, 2, 0>(mode) : static_lds_mode<BS, 2, 1>(mode);
-    case CPHOT_TRANSPORT_CURVED: return static_lds_mode<BS, 3, 0>(mode);
-    case kTransportCurvedWalk: return static_lds_mode<BS, kTransportCurvedWalk, 0>(mode);
-    case CPHOT_TRANSPORT_TABLE: return g ? static_lds_mode<BS, 4, 0>(mode) : static_lds_mode<BS, 4, 1>(mode);
-    case kTransportCurvedTable: return static_lds_mode<BS, kTransportCurvedTable, 0>(mode);
-    default: return static_lds_mode<BS, kTransportCurvedSurrogate, 0>(mode);
+    case CPHOT_TRANSPORT_STRAIGHT: return g ? info_one<BS, 0, 0>() : info_one<BS, 0, 1>();
+    case CPHOT_TRANSPORT_LAYERED: return g ? info_one<BS, 1, 0>() : info_one<BS, 1, 1>();
+    case CPHOT_TRANSPORT_SURROGATE: return g ? info_one<BS, 2, 0>() : info_one<BS, 2, 1>();
+    case CPHOT_TRANSPORT_CURVED: return info_one<BS, 3, 0>();
+    case kTransportCurvedWalk: return info_one<BS, kTransportCurvedWalk, 0>();
+    case CPHOT_TRANSPORT_TABLE: return g ? info_one<BS, 4, 0>() : info_one<BS, 4, 1>();
+    case kTransportCurvedTable: return info_one<BS, kTransportCurvedTable, 0>();
+    default: return info_one<BS, kTransportCurvedSurrogate, 0>();
   }
 }
+#endif
 
-}  // namespace
-
-size_t propagate_static_lds(const KParams& p, int mode, int block_size) {
+#if CPHOT_BLOCK == 256
+KernelInfo propagate_info(const KParams& p, int block_size) {
   switch (block_size) {
-    case 128: return static_lds_bs<128>(p, mode);
-    case 512: return static_lds_bs<512>(p, mode);
-    default: return static_lds_bs<256>(p, mode);
+    case 128: return info_block<128>(p);
+    case 512: return info_block<512>(p);
+    case kBigBlock: return info_block<1024>(p);
+    default: return info_block<256>(p);
   }
 }
 
 hipError_t launch_propagate(const KParams& p, int mode, int block_size, int grid_blocks, size_t lds_bytes,
                             hipStream_t stream) {
+  if (mode == MODE_COUNTS) {
+    if (p.poisson || p.spectrum == CPHOT_SPECTRUM_DISPERSIVE)
+      hipLaunchKernelGGL(k_counts<true>, dim3(grid_blocks), dim3(256), 0, stream, p);
+    else
+      hipLaunchKernelGGL(k_counts<false>, dim3(grid_blocks), dim3(256), 0, stream, p);
+    return hipGetLastError();
+  }
+  const dim3 grid(grid_blocks);
   switch (block_size) {
-    case 128: return launch_bs<128>(p, mode, grid_blocks, lds_bytes, stream);
-    case 512: return launch_bs<512>(p, mode, grid_blocks, lds_bytes, stream);
-    default: return launch_bs<256>(p, mode, grid_blocks, lds_bytes, stream);
+    case 128: return launch_block<128>(p, mode, grid, lds_bytes, stream);
+    case 512: return launch_block<512>(p, mode, grid, lds_bytes, stream);
+    case kBigBlock: return launch_block<1024>(p, mode, grid, lds_bytes, stream);
+    default: return launch_block<256>(p, mode, grid, lds_bytes, stream);
   }
 }
+#endif
 
 }  // namespace cphot
