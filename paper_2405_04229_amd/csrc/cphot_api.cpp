@@ -448,10 +448,22 @@ void grow_window(int& w, int& h, int nx, int ny, size_t area) {
 // Against one block of 256 per 256 segments with device atomics: inclined shower of 1e6
 // segments with the correction table 7.7 -> 2.2 ms, with the network 8.2 -> 3.2 ms.
 //
-// A launch with fewer tiles of 64 segments than waves on the chip shares each tile's
-// record rounds among 2^k units (the tile's set-up is repeated on waves that would idle):
-// k as small as fills the chip, at most 4. 1e4 segments on straight rays, k = 0, 2, 4, 6:
-// 129, 44, 23, 27 us; 2e4 on refracted ones: 135, 53, 38, 55 us.
+// A tile's record rounds can be shared by 2^k units of work (work_shift). More units
+// balance the waves at the end of a launch and fill the chip when tiles are few; each
+// repeats the tile's set-up, which costs as much as a few rounds. With r rounds a tile and
+// `fill` waves on the chip the two costs are even near 4^k = 0.45 r fill / tiles. r is not
+// known before the launch: tens of photons per segment, fewer rounds with larger bunches
+// and where cuts or the pre-emission reduction remove most records. Measured (us, k = 0..4):
+// 1e4 segments straight 129 71 44 30 23; 1e5 layered 137 78 70 69 82; 4.3e5 in 66 showers
+// straight 435 288 251 260 320, in bunches of 5 136 109 115 138 201; 4e5 curved 1296 1274
+// 1115 1113 1163; 1e6 on spheres in bunches of 5 139 158 203 287 463.
+int work_shift(const cphot_detector* det, int64_t tiles, int64_t fill) {
+  double r = 40.0 / det->bunch;
+  if ((det->cuts & CPHOT_CUT_TRACK) || det->reduction) r *= 0.25;
+  const double x = 0.45 * r * (double)fill / (double)std::max<int64_t>(tiles, 1);
+  return x > 1.0 ? std::min(4, (int)std::lround(0.5 * std::log2(x))) : 0;
+}
+
 int choose_shape(const cphot_detector* det, cphot::KParams& p, int mode, LaunchShape& s) {
   if (det->block_size != 0 && det->block_size != 128 && det->block_size != 256 && det->block_size != 512)
     return fail(CPHOT_ERR_INVALID_ARG, "block_size must be 0, 128, 256 or 512");
@@ -542,7 +554,7 @@ int choose_shape(const cphot_detector* det, cphot::KParams& p, int mode, LaunchS
   }
   const int64_t tiles = (p.n + 63) / 64;
   const int64_t fill = cus * per_cu * waves;  // waves on the chip
-  while (mode != cphot::MODE_COUNTS && p.sub_shift < 4 && (tiles << p.sub_shift) < fill) ++p.sub_shift;
+  if (mode != cphot::MODE_COUNTS) p.sub_shift = work_shift(det, tiles, fill);
   const int64_t most = ((tiles << p.sub_shift) + waves - 1) / waves;
   // a persistent grid fills the chip once and amortises the tables and the window; without
   // LDS counts one unit per wave lets the dispatcher balance uneven tiles
