@@ -24,16 +24,7 @@ namespace cphot {
 
 namespace {
 
-constexpr int kTrainWave = 64;  // samples per training block (one wave)
-
-// c += A[16 x 32] * B[32 x 16] with A rows and B columns stored k-contiguous
-// (row r of A at A + r * lda, column n of B at Bt + n * ldb).
-__device__ __forceinline__ f32x4 mma_kc(const __bf16* A, int lda, const __bf16* Bt, int ldb, f32x4 c) {
-  const int l = threadIdx.x & 63;
-  const bf16x8 a = *reinterpret_cast<const bf16x8*>(A + (l & 15) * lda + (l >> 4) * 8);
-  const bf16x8 b = *reinterpret_cast<const bf16x8*>(Bt + (l & 15) * ldb + (l >> 4) * 8);
-  return mfma16(a, b, c);
-}
+constexpr int kTrainWave = 64;  // samples per training block
 
 __device__ __forceinline__ f32x4 zero4() { return f32x4{0.f, 0.f, 0.f, 0.f}; }
 
@@ -293,159 +284,234 @@ struct StepParams {
   float* loss_partial;
 };
 
-// One wave, 64 samples: forward, loss, backward; writes this block's share of
-// the gradient of mean((y_hat - t_hat)^2) over the whole batch.
-__global__ __launch_bounds__(64) void k_train_step(StepParams p) {
-  __shared__ __attribute__((aligned(16))) __bf16 Xh[64][32];
-  __shared__ __attribute__((aligned(16))) __bf16 XhT[32][64];
-  __shared__ __attribute__((aligned(16))) __bf16 H1[64][64];
-  __shared__ __attribute__((aligned(16))) __bf16 H1T[64][64];  // later dZ1^T
-  __shared__ __attribute__((aligned(16))) __bf16 H2[64][64];   // later dZ2
-  __shared__ __attribute__((aligned(16))) __bf16 H2T[64][64];  // later dZ2^T
-  __shared__ __attribute__((aligned(16))) __bf16 dY[64][32];
-  __shared__ __attribute__((aligned(16))) __bf16 dYT[16][64];
-  const int l = threadIdx.x;
+// A row of 64 activations in LDS: padded so that the 16 rows of an operand start in
+// different banks.
+constexpr int kRow = 72;
+
+// Operand of 16 rows x 32 k from LDS rows (k-contiguous), row l % 16, k = 8 (l / 16) + i.
+__device__ __forceinline__ bf16x8 lds_op(const __bf16* rows) {
+  const int l = threadIdx.x & 63;
+  return *reinterpret_cast<const bf16x8*>(rows + (l & 15) * kRow + (l >> 4) * 8);
+}
+
+__device__ __forceinline__ bf16x8 global_op(const __bf16* rows, int ld) {
+  const int l = threadIdx.x & 63;
+  return *reinterpret_cast<const bf16x8*>(rows + (l & 15) * ld + (l >> 4) * 8);
+}
+
+__device__ __forceinline__ bf16x8 zero_op() {
+  bf16x8 v;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] = (__bf16)0.f;
+  return v;
+}
+
+// Four values of a column (rows 4 g .. 4 g + 3), contiguous in the transposed array.
+__device__ __forceinline__ void store4(__bf16* at, const __bf16 v[4]) {
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  *reinterpret_cast<bf16x4*>(at) = (bf16x4){v[0], v[1], v[2], v[3]};
+}
+
+// Sum of a row of 64 in order.
+__device__ __forceinline__ float row_sum(const __bf16* row) {
+  float sb = 0.f;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const bf16x8 v = *reinterpret_cast<const bf16x8*>(row + 8 * q);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sb += (float)v[i];
+  }
+  return sb;
+}
+
+// 64 samples on four waves: forward, loss, backward; writes this block's share of
+// the gradient of mean((y_hat - t_hat)^2) over the whole batch. The step is bound by
+// latency (a chain of five small products, 64 blocks at the usual batch): a wave carries
+// 16 samples through all layers and back with no block barrier, all weight operands are
+// loaded at the start with the samples, and only the weight gradients, whose sums run
+// over the 64 samples, meet in one barrier, a quarter of them per wave. Every product
+// and sum keeps the order that one wave doing all of it had (15.2 -> 6.5 us, batch 4096).
+__global__ __launch_bounds__(256) void k_train_step(StepParams p) {
+  __shared__ __attribute__((aligned(16))) __bf16 H1[64][kRow], H1T[64][kRow];
+  __shared__ __attribute__((aligned(16))) __bf16 H2[64][kRow], H2T[64][kRow];  // H2: then dZ2
+  __shared__ __attribute__((aligned(16))) __bf16 Z2T[64][kRow], Z1T[64][kRow];
+  __shared__ __attribute__((aligned(16))) __bf16 XhT[8][kRow], dY[64][8], dYT[4][kRow];
+  __shared__ float sq[16][64];  // squared residuals, row 4 (sample / 16) + r, lane
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int g = l >> 4, c = l & 15;
   const float* norm = p.norm;
-  const int64_t s0 = p.start + (int64_t)blockIdx.x * kTrainWave;
-  // scaled inputs of sample l
-  {
-    const int64_t js = (s0 + l) % p.n;
-    for (int k = 0; k < 32; ++k) {
-      float v = 0.f;
-      if (k < 5) v = fmaf(p.X[5 * js + k] - norm[k], norm[10 + k], -1.0f);
-      const __bf16 b = (__bf16)v;
-      Xh[l][k] = b;
-      XhT[k][l] = b;
-    }
-    for (int o = 0; o < 32; ++o) dY[l][o] = (__bf16)0.f;
-    for (int o = 0; o < 16; ++o) dYT[o][l] = (__bf16)0.f;
-  }
-  __syncthreads();
-  const TrainWeights* tw = p.tw;
   const float* m = p.master;
-  // ---- forward, rows = samples
-  for (int mt = 0; mt < 4; ++mt)
-    for (int nt = 0; nt < 4; ++nt) {
-      f32x4 acc;
-      for (int r = 0; r < 4; ++r) acc[r] = m[kOffB1 + 16 * nt + c];
-      acc = mma_kc(&Xh[16 * mt][0], 32, &tw->w1t[16 * nt][0], 32, acc);
-      for (int r = 0; r < 4; ++r) {
-        const int s = 16 * mt + 4 * g + r, j = 16 * nt + c;
-        const __bf16 h = (__bf16)fmaxf(acc[r], 0.f);
-        H1[s][j] = h;
-        H1T[j][s] = h;
-      }
+  const TrainWeights* tw = p.tw;
+  const int64_t s0 = p.start + (int64_t)blockIdx.x * kTrainWave;
+  auto sample = [&](int s) {  // start < n and batch <= n: wraps at most once
+    const int64_t j = s0 + s;
+    return j < p.n ? j : j - p.n;
+  };
+  // ---- everything the chain reads from memory
+  bf16x8 w1[4], w2t[4][2], w3t[2], w3[4], w2[4][2];
+  float b1[4], b2[4], x[5], t[4];
+#pragma unroll
+  for (int k = 0; k < 5; ++k) x[k] = p.X[5 * sample(16 * w + c) + k];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) t[r] = p.Y[4 * sample(16 * w + 4 * g + r) + (c & 3)];
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt) {
+    w1[nt] = global_op(&tw->w1t[16 * nt][0], 32);
+    b1[nt] = m[kOffB1 + 16 * nt + c];
+  }
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt) {
+    w2t[nt][0] = global_op(&tw->w2t[16 * nt][0], 64);
+    w2t[nt][1] = global_op(&tw->w2t[16 * nt][32], 64);
+    b2[nt] = m[kOffB2 + 16 * nt + c];
+  }
+  w3t[0] = global_op(&tw->w3t[0][0], 64);
+  w3t[1] = global_op(&tw->w3t[0][32], 64);
+  const float b3 = c < 4 ? m[kOffB3 + c] : 0.f;
+  const float mean = norm[16 + (c & 3)], std = norm[20 + (c & 3)];
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt) w3[nt] = global_op(&tw->w3[16 * nt][0], 32);
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt) {
+    w2[nt][0] = global_op(&tw->w2[16 * nt][0], 64);
+    w2[nt][1] = global_op(&tw->w2[16 * nt][32], 64);
+  }
+  // ---- forward, rows = this wave's 16 samples
+  bf16x8 xa = zero_op();  // k = 0..4 in the lanes g == 0
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    const __bf16 b = (__bf16)fmaf(x[k] - norm[k], norm[10 + k], -1.0f);
+    if (g == 0) {
+      xa[k] = b;
+      XhT[k][16 * w + c] = b;
     }
-  __syncthreads();
-  for (int mt = 0; mt < 4; ++mt)
-    for (int nt = 0; nt < 4; ++nt) {
-      f32x4 acc;
-      for (int r = 0; r < 4; ++r) acc[r] = m[kOffB2 + 16 * nt + c];
-      for (int kt = 0; kt < 2; ++kt) acc = mma_kc(&H1[16 * mt][32 * kt], 64, &tw->w2t[16 * nt][32 * kt], 64, acc);
-      for (int r = 0; r < 4; ++r) {
-        const int s = 16 * mt + 4 * g + r, j = 16 * nt + c;
-        const __bf16 h = (__bf16)fmaxf(acc[r], 0.f);
-        H2[s][j] = h;
-        H2T[j][s] = h;
-      }
+  }
+  __bf16 h1[4][4], h2[4][4];
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt) {
+    f32x4 acc = {b1[nt], b1[nt], b1[nt], b1[nt]};
+    acc = mfma16(xa, w1[nt], acc);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      h1[nt][r] = (__bf16)fmaxf(acc[r], 0.f);
+      H1[16 * w + 4 * g + r][16 * nt + c] = h1[nt][r];
     }
-  __syncthreads();
-  float loss = 0.f;
-  const float dscale = 2.0f / (4.0f * (float)p.batch);
-  for (int mt = 0; mt < 4; ++mt) {
-    f32x4 acc;
-    for (int r = 0; r < 4; ++r) acc[r] = c < 4 ? m[kOffB3 + c] : 0.f;
-    for (int kt = 0; kt < 2; ++kt) acc = mma_kc(&H2[16 * mt][32 * kt], 64, &tw->w3t[0][32 * kt], 64, acc);
-    if (c < 4) {
+    store4(&H1T[16 * nt + c][16 * w + 4 * g], h1[nt]);
+  }
+  wave_fence();
+  {
+    const bf16x8 a0 = lds_op(&H1[16 * w][0]), a1 = lds_op(&H1[16 * w][32]);
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+      f32x4 acc = {b2[nt], b2[nt], b2[nt], b2[nt]};
+      acc = mfma16(a0, w2t[nt][0], acc);
+      acc = mfma16(a1, w2t[nt][1], acc);
+#pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int s = 16 * mt + 4 * g + r;
-        const int64_t js = (s0 + s) % p.n;
-        const float t = (p.Y[4 * js + c] - norm[16 + c]) / norm[20 + c];
-        const float d = acc[r] - t;
-        loss += d * d;
-        const __bf16 db = (__bf16)(d * dscale);
-        dY[s][c] = db;
-        dYT[c][s] = db;
+        h2[nt][r] = (__bf16)fmaxf(acc[r], 0.f);
+        H2[16 * w + 4 * g + r][16 * nt + c] = h2[nt][r];
       }
+      store4(&H2T[16 * nt + c][16 * w + 4 * g], h2[nt]);
+    }
+  }
+  wave_fence();
+  {
+    f32x4 acc = {b3, b3, b3, b3};
+    acc = mfma16(lds_op(&H2[16 * w][0]), w3t[0], acc);
+    acc = mfma16(lds_op(&H2[16 * w][32]), w3t[1], acc);
+    const float dscale = 2.0f / (4.0f * (float)p.batch);
+    __bf16 db[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float d = acc[r] - (t[r] - mean) / std;
+      sq[4 * w + r][l] = c < 4 ? d * d : 0.f;
+      db[r] = (__bf16)(c < 4 ? d * dscale : 0.f);
+      if (c < 8) dY[16 * w + 4 * g + r][c] = db[r];  // outputs 4..7: zero
+    }
+    if (c < 4) store4(&dYT[c][16 * w + 4 * g], db);
+  }
+  wave_fence();
+  // ---- backward through the layers
+  {
+    const bf16x8 dy = g == 0 ? *reinterpret_cast<const bf16x8*>(&dY[16 * w + c][0]) : zero_op();
+    // dZ2[s][j] = (sum_o dY[s][o] W3[j][o]) * (H2[s][j] > 0)
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+      const f32x4 acc = mfma16(dy, w3[nt], zero4());
+      __bf16 z[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        z[r] = (__bf16)((float)h2[nt][r] > 0.f ? acc[r] : 0.f);
+        H2[16 * w + 4 * g + r][16 * nt + c] = z[r];
+      }
+      store4(&Z2T[16 * nt + c][16 * w + 4 * g], z);
+    }
+  }
+  wave_fence();
+  {
+    // dZ1[s][i] = (sum_j dZ2[s][j] W2[i][j]) * (H1[s][i] > 0)
+    const bf16x8 a0 = lds_op(&H2[16 * w][0]), a1 = lds_op(&H2[16 * w][32]);
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+      f32x4 acc = mfma16(a0, w2[nt][0], zero4());
+      acc = mfma16(a1, w2[nt][1], acc);
+      __bf16 z[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) z[r] = (__bf16)((float)h1[nt][r] > 0.f ? acc[r] : 0.f);
+      store4(&Z1T[16 * nt + c][16 * w + 4 * g], z);
     }
   }
   __syncthreads();
+  // ---- weight gradients over the 64 samples, a quarter per wave
   float* part = p.partial + (size_t)blockIdx.x * kMlpParams;
-  // ---- backward
-  // dW3[j][o] = sum_s H2^T[j][s] dY^T[o][s]
-  for (int mj = 0; mj < 4; ++mj) {
-    f32x4 acc = zero4();
-    for (int ks = 0; ks < 2; ++ks) acc = mma_kc(&H2T[16 * mj][32 * ks], 64, &dYT[0][32 * ks], 64, acc);
-    if (c < 4)
-      for (int r = 0; r < 4; ++r) part[kOffW3 + (16 * mj + 4 * g + r) * 4 + c] = acc[r];
-  }
-  if (l < 4) {
-    float sb = 0.f;
-    for (int s = 0; s < 64; ++s) sb += (float)dYT[l][s];
-    part[kOffB3 + l] = sb;
-  }
-  __syncthreads();
-  // dZ2[s][j] = (sum_o dY[s][o] W3[j][o]) * (H2[s][j] > 0), into H2 and H2T
-  for (int mt = 0; mt < 4; ++mt)
-    for (int nt = 0; nt < 4; ++nt) {
-      f32x4 acc = zero4();
-      acc = mma_kc(&dY[16 * mt][0], 32, &tw->w3[16 * nt][0], 32, acc);
-      for (int r = 0; r < 4; ++r) {
-        const int s = 16 * mt + 4 * g + r, j = 16 * nt + c;
-        const bool on = (float)H2[s][j] > 0.f;
-        const __bf16 d = (__bf16)(on ? acc[r] : 0.f);
-        H2[s][j] = d;
-        H2T[j][s] = d;
-      }
-    }
-  __syncthreads();
-  // dW2[i][j] = sum_s H1^T[i][s] dZ2^T[j][s]; db2 = row sums of dZ2^T
-  for (int mi = 0; mi < 4; ++mi)
+  {
+    // dW2[i][j] = sum_s H1^T[i][s] dZ2^T[j][s], rows i = 16 w ..
+    const bf16x8 a0 = lds_op(&H1T[16 * w][0]), a1 = lds_op(&H1T[16 * w][32]);
+#pragma unroll
     for (int nj = 0; nj < 4; ++nj) {
-      f32x4 acc = zero4();
-      for (int ks = 0; ks < 2; ++ks) acc = mma_kc(&H1T[16 * mi][32 * ks], 64, &H2T[16 * nj][32 * ks], 64, acc);
-      for (int r = 0; r < 4; ++r) part[kOffW2 + (16 * mi + 4 * g + r) * 64 + 16 * nj + c] = acc[r];
+      f32x4 acc = mfma16(a0, lds_op(&Z2T[16 * nj][0]), zero4());
+      acc = mfma16(a1, lds_op(&Z2T[16 * nj][32]), acc);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) part[kOffW2 + (16 * w + 4 * g + r) * 64 + 16 * nj + c] = acc[r];
     }
-  {
-    float sb = 0.f;
-    for (int s = 0; s < 64; ++s) sb += (float)H2T[l][s];
-    part[kOffB2 + l] = sb;
+    // dW3[j][o] = sum_s H2^T[j][s] dY^T[o][s]
+    bf16x8 d0 = zero_op(), d1 = zero_op();
+    if (c < 4) {
+      d0 = *reinterpret_cast<const bf16x8*>(&dYT[c][8 * g]);
+      d1 = *reinterpret_cast<const bf16x8*>(&dYT[c][32 + 8 * g]);
+    }
+    f32x4 acc = mfma16(lds_op(&H2T[16 * w][0]), d0, zero4());
+    acc = mfma16(lds_op(&H2T[16 * w][32]), d1, acc);
+    if (c < 4) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) part[kOffW3 + (16 * w + 4 * g + r) * 4 + c] = acc[r];
+    }
+    // dW1[k][i] = sum_s Xh^T[k][s] dZ1^T[i][s], columns i = 16 w ..
+    bf16x8 x0 = zero_op(), x1 = zero_op();
+    if (c < 5) {
+      x0 = *reinterpret_cast<const bf16x8*>(&XhT[c][8 * g]);
+      x1 = *reinterpret_cast<const bf16x8*>(&XhT[c][32 + 8 * g]);
+    }
+    acc = mfma16(x0, lds_op(&Z1T[16 * w][0]), zero4());
+    acc = mfma16(x1, lds_op(&Z1T[16 * w][32]), acc);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (4 * g + r < 5) part[kOffW1 + (4 * g + r) * 64 + 16 * w + c] = acc[r];
   }
-  // dZ1[s][i] = (sum_j dZ2[s][j] W2[i][j]) * (H1[s][i] > 0)
-  float dz1[4][4][4];
-  for (int mt = 0; mt < 4; ++mt)
-    for (int ni = 0; ni < 4; ++ni) {
-      f32x4 acc = zero4();
-      for (int kt = 0; kt < 2; ++kt) acc = mma_kc(&H2[16 * mt][32 * kt], 64, &tw->w2[16 * ni][32 * kt], 64, acc);
-      for (int r = 0; r < 4; ++r) {
-        const int s = 16 * mt + 4 * g + r, i = 16 * ni + c;
-        dz1[mt][ni][r] = ((float)H1[s][i] > 0.f) ? acc[r] : 0.f;
-      }
-    }
-  __syncthreads();  // H1^T (read by dW2 above) is free now
-  for (int mt = 0; mt < 4; ++mt)
-    for (int ni = 0; ni < 4; ++ni)
-      for (int r = 0; r < 4; ++r) H1T[16 * ni + c][16 * mt + 4 * g + r] = (__bf16)dz1[mt][ni][r];
-  __syncthreads();
-  // dW1[k][i] = sum_s Xh^T[k][s] dZ1^T[i][s] (k < 5 kept); db1 = row sums of dZ1^T
-  for (int mk = 0; mk < 2; ++mk)
-    for (int ni = 0; ni < 4; ++ni) {
-      f32x4 acc = zero4();
-      for (int ks = 0; ks < 2; ++ks) acc = mma_kc(&XhT[16 * mk][32 * ks], 64, &H1T[16 * ni][32 * ks], 64, acc);
-      for (int r = 0; r < 4; ++r) {
-        const int k = 16 * mk + 4 * g + r;
-        if (k < 5) part[kOffW1 + k * 64 + 16 * ni + c] = acc[r];
-      }
-    }
-  {
-    float sb = 0.f;
-    for (int s = 0; s < 64; ++s) sb += (float)H1T[l][s];
-    part[kOffB1 + l] = sb;
+  // bias gradients and the loss share, one per wave
+  if (w == 0) {
+    part[kOffB2 + l] = row_sum(&Z2T[l][0]);
+  } else if (w == 1) {
+    part[kOffB1 + l] = row_sum(&Z1T[l][0]);
+  } else if (w == 2) {
+    if (l < 4) part[kOffB3 + l] = row_sum(&dYT[l][0]);
+  } else {
+    float loss = 0.f;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) loss += sq[q][l];
+    for (int d = 32; d >= 1; d >>= 1) loss += __shfl_xor(loss, d, 64);
+    if (l == 0) p.loss_partial[blockIdx.x] = loss;
   }
-  // loss share
-  for (int d = 32; d >= 1; d >>= 1) loss += __shfl_xor(loss, d, 64);
-  if (l == 0) p.loss_partial[blockIdx.x] = loss;
 }
 
 // Sum of the block partials (fixed order: deterministic) -> grad; optionally
@@ -469,33 +535,59 @@ struct AdamParams {
   int update;
 };
 
-__global__ __launch_bounds__(256) void k_adam(AdamParams p) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  const int t = p.t;
-  if (i < kMlpParams) {
-    float gsum = 0.f;
-    for (int b = 0; b < p.blocks; ++b) gsum += p.partial[(size_t)b * kMlpParams + i];
-    if (p.grad_out) p.grad_out[i] = gsum;
-    if (p.update) {
-      const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-      const float tt = (float)(t + 1);
-      const float prog = p.total_steps > 1 ? (float)p.loss_index / (float)(p.total_steps - 1) : 0.f;
-      const float lr = p.lr * (0.01f + 0.99f * 0.5f * (1.f + cosf(3.14159265f * fminf(prog, 1.f))));
-      const float m1 = b1 * p.m1[i] + (1.f - b1) * gsum;
-      const float m2 = b2 * p.m2[i] + (1.f - b2) * gsum * gsum;
-      p.m1[i] = m1;
-      p.m2[i] = m2;
-      const float mh = m1 / (1.f - powf(b1, tt));
-      const float vh = m2 / (1.f - powf(b2, tt));
-      const float w = p.master[i] - lr * mh / (sqrtf(vh) + eps);
-      p.master[i] = w;
-      scatter_param(i, w, p.tw, p.img);
-    }
-  }
-  if (i == 0 && p.loss_out) {
+// One wave per 64 parameters (and one for the loss), so that the 76 waves sit on as many
+// CUs. Bound by the latency of the partials, which other XCDs wrote: 32 loads are in
+// flight per lane, the additions keep their order (19.7 -> 4.7 us at 64 partials, where each
+// load waited for the addition before it).
+__global__ __launch_bounds__(64) void k_adam(AdamParams p) {
+  constexpr int kFly = 64;
+  const int l = threadIdx.x;
+  if (blockIdx.x == gridDim.x - 1) {  // loss of this step
+    if (!p.loss_out) return;
     float ls = 0.f;
-    for (int b = 0; b < p.blocks; ++b) ls += p.loss_partial[b];
-    p.loss_out[p.loss_index] = ls / (4.0f * (float)p.batch);
+    for (int b0 = 0; b0 < p.blocks; b0 += 64) {
+      const float v = b0 + l < p.blocks ? p.loss_partial[b0 + l] : 0.f;
+      for (int q = 0; q < min(64, p.blocks - b0); ++q)
+        ls += __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), q));
+    }
+    if (l == 0) p.loss_out[p.loss_index] = ls / (4.0f * (float)p.batch);
+    return;
+  }
+  const int i = blockIdx.x * 64 + l;
+  if (i >= kMlpParams) return;
+  const float* part = p.partial + i;
+  float m1 = 0.f, m2 = 0.f, w = 0.f;
+  if (p.update) {
+    m1 = p.m1[i];
+    m2 = p.m2[i];
+    w = p.master[i];
+  }
+  float gsum = 0.f;
+  int b = 0;
+  for (; b + kFly <= p.blocks; b += kFly) {
+    float v[kFly];
+#pragma unroll
+    for (int q = 0; q < kFly; ++q) v[q] = part[(size_t)(b + q) * kMlpParams];
+#pragma unroll
+    for (int q = 0; q < kFly; ++q) gsum += v[q];
+  }
+  for (; b < p.blocks; ++b) gsum += part[(size_t)b * kMlpParams];
+  if (p.grad_out) p.grad_out[i] = gsum;
+  if (p.update) {
+    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+    const float tt = (float)(p.t + 1);
+    const float prog = p.total_steps > 1 ? (float)p.loss_index / (float)(p.total_steps - 1) : 0.f;
+    const float lr = p.lr * (0.01f + 0.99f * 0.5f * (1.f + cosf(3.14159265f * fminf(prog, 1.f))));
+    const float c1 = 1.f - powf(b1, tt), c2 = 1.f - powf(b2, tt);
+    m1 = b1 * m1 + (1.f - b1) * gsum;
+    m2 = b2 * m2 + (1.f - b2) * gsum * gsum;
+    p.m1[i] = m1;
+    p.m2[i] = m2;
+    const float mh = m1 / c1;
+    const float vh = m2 / c2;
+    w = w - lr * mh / (sqrtf(vh) + eps);
+    p.master[i] = w;
+    scatter_param(i, w, p.tw, p.img);
   }
 }
 
@@ -530,7 +622,7 @@ __global__ __launch_bounds__(256) void k_forward(const MlpImage* __restrict__ im
 // ================================================================================ host API
 
 // Per-block partial gradients and loss shares of cphot_surrogate_gradient_noalloc:
-// at most kNoAllocSamples samples, i.e. kNoAllocSamples / 64 single-wave blocks, each
+// at most kNoAllocSamples samples, i.e. kNoAllocSamples / 64 blocks, each
 // writing all kMlpParams entries of its row and its loss share (so nothing needs
 // clearing between calls). 1.23 MB per device, held until the process ends. In host
 // code `scratch` only names the symbol: its device address comes from
@@ -759,7 +851,7 @@ static int run_steps(cphot_surrogate* s, const float* X, const float* Y, int64_t
     sp.tw = s->tw;
     sp.partial = partial;
     sp.loss_partial = loss_partial;
-    hipLaunchKernelGGL(cphot::k_train_step, dim3(blocks), dim3(64), 0, st, sp);
+    hipLaunchKernelGGL(cphot::k_train_step, dim3(blocks), dim3(256), 0, st, sp);
     cphot::AdamParams ap;
     ap.partial = partial;
     ap.loss_partial = loss_partial;
@@ -777,7 +869,7 @@ static int run_steps(cphot_surrogate* s, const float* X, const float* Y, int64_t
     ap.loss_index = k;
     ap.batch = batch;
     ap.update = update;
-    hipLaunchKernelGGL(cphot::k_adam, dim3((cphot::kMlpParams + 255) / 256), dim3(256), 0, st, ap);
+    hipLaunchKernelGGL(cphot::k_adam, dim3((cphot::kMlpParams + 63) / 64 + 1), dim3(64), 0, st, ap);
     if (update) ++s->steps_done;
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return shfail(e, "training step");
