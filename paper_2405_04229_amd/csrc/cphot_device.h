@@ -217,12 +217,9 @@ struct LayerWalk {
   float vx, vy, vz;
   float tau;         // optical depth accumulated above the observation layer
   float geo;         // sum of l (1 - u . axis)                               (NEED_TIME)
-  float opt;         // sum of (n - 1) l                                       (NEED_TIME or NEED_EXCESS)
-  float dr;          // horizontal travel beyond the straight line, along the azimuth (NEED_EXCESS)
-  float gex;         // geometric path beyond the straight line                (NEED_EXCESS)
+  float opt;         // sum of (n - 1) l                                       (NEED_TIME)
   float last_delta;  // n - 1 of the observation layer
   float last_ext;    // extinction per metre there
-  float s0, c0, d0, hx, hy;  // start sine and cosine, start n - 1, azimuth
 };
 
 // Sine and squared cosine in a layer with n - 1 = d, 1/n = inv_n.
@@ -233,22 +230,7 @@ __device__ __forceinline__ void layer_angle(float s0, float c0, float d0, float 
   c2 = fmaxf(fmaf(s0 * s0 * e, 2.0f - e, c0 * c0), 1e-30f);
 }
 
-// Excess of a leg of vertical extent `span` crossed at sine s (layer with
-// n - 1 = d, 1/n = inv_n) over the same extent crossed at the start sine s0:
-// returns horizontal and path excess without subtracting nearly equal
-// lengths (s - s0 = -s0 e).
-__device__ __forceinline__ void leg_excess(const LayerWalk& w, float span, float d, float inv_n, float& dr,
-                                           float& gex) {
-  float s, c2, e;
-  layer_angle(w.s0, w.c0, w.d0, d, inv_n, s, c2, e);
-  const float c = sqrtf(c2);
-  const float dsq = -w.s0 * e * (s + w.s0);  // s^2 - s0^2
-  const float den = s * w.c0 + w.s0 * c;     // zero only for a vertical photon, whose offset is zero
-  if (den > 0.f) dr = fmaf(span, dsq / (den * c * w.c0), dr);
-  gex = fmaf(span, dsq / (c * w.c0 * (c + w.c0)), gex);
-}
-
-template <bool NEED_TIME, bool NEED_EXCESS>
+template <bool NEED_TIME>
 __device__ __forceinline__ void layer_walk(const float4* __restrict__ lay, float2 sp, float dh, int i,
                                            int obs_layer, float Px, float Py, float Pz, float ux, float uy,
                                            float uz, float axx, float axy, float axz, LayerWalk& w) {
@@ -261,13 +243,6 @@ __device__ __forceinline__ void layer_walk(const float4* __restrict__ lay, float
   }
   float4 L = lay[i];
   const float s0 = sh, c0 = -uz, d0 = L.x;
-  w.d0 = d0;
-  w.s0 = s0;
-  w.c0 = c0;
-  w.hx = hx;
-  w.hy = hy;
-  w.dr = 0.f;
-  w.gex = 0.f;
   float x = Px, y = Py, z = Pz, tau = 0.f, geo2 = 0.f, opt = 0.f;
   // geometric delay per unit path 1 - v.a = |v - a|^2 / 2, v = (s h, -c), formed
   // from the differences so that no near-1 quantity is subtracted; the factor
@@ -288,8 +263,7 @@ __device__ __forceinline__ void layer_walk(const float4* __restrict__ lay, float
       const float ex = fmaf(s, hx, nax), ey = fmaf(s, hy, nay), ez = fmaf(-c2, ic, naz);
       geo2 = fmaf(path, fmaf(ex, ex, fmaf(ey, ey, ez * ez)), geo2);
     }
-    if constexpr (NEED_TIME || NEED_EXCESS) opt = fmaf(L.x, path, opt);
-    if constexpr (NEED_EXCESS) leg_excess(w, span, L.x, L.y, w.dr, w.gex);
+    if constexpr (NEED_TIME) opt = fmaf(L.x, path, opt);
     z = zb;
     --i;
     L = lay[i];
@@ -380,13 +354,6 @@ __device__ __forceinline__ void layer_series(const float4* __restrict__ lay, con
   w.vz = -c;
   w.last_delta = Lo.x;
   w.last_ext = fmaf(Lo.z, sp.x, Lo.w * sp.y);
-  w.s0 = s0;
-  w.c0 = c0;
-  w.d0 = Lj.x;
-  w.hx = hx;
-  w.hy = hy;
-  w.dr = 0.f;
-  w.gex = 0.f;
 }
 
 // Curved Earth (Sec. 3.3.4): the layers are spherical shells about the Earth

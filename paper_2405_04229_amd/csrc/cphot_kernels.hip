@@ -786,7 +786,7 @@ __device__ __forceinline__ void trace(const K& H, const KParams& p, const Tables
         layer_series<NEED_TIME>(s_lay, H.moments, s_lam[kb], H.dh, j0, H.obs_layer, Px, Py, Pz, ux, uy, uz, axx,
                                 axy, axz, lw);
       else
-        layer_walk<NEED_TIME, false>(s_lay, s_lam[kb], H.dh, j0, H.obs_layer, Px, Py, Pz, ux, uy, uz, axx, axy,
+        layer_walk<NEED_TIME>(s_lay, s_lam[kb], H.dh, j0, H.obs_layer, Px, Py, Pz, ux, uy, uz, axx, axy,
                                      axz, lw);
       x = lw.x;
       y = lw.y;

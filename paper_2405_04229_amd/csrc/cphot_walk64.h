@@ -138,6 +138,67 @@ __device__ inline bool shell_walk_f64(const float4* __restrict__ lay, double dh,
   return false;
 }
 
+// Reciprocal and square root of positive, normal doubles by Newton's iteration from the
+// hardware's estimates, within two units in the last place (the walk's sums are rounded to
+// FP32 afterwards).
+__device__ __forceinline__ double rcp_f64(double a) {
+  double y = __builtin_amdgcn_rcp(a);
+  y = fma(fma(-a, y, 1.0), y, y);
+  return fma(fma(-a, y, 1.0), y, y);
+}
+__device__ __forceinline__ double sqrt_f64(double a) {
+  const double y = __builtin_amdgcn_rsq(a);
+  double g = a * y, h = 0.5 * y;
+  double r = fma(-h, g, 0.5);
+  g = fma(g, r, g);
+  h = fma(h, r, h);
+  r = fma(-g, g, a);
+  return fma(r, h, g);
+}
+
+// The sums of shell_walk_f64 for a ray that goes straight down through every shell, as
+// nearly all do (nd[i] = n - 1 and 1 / n of shell i): one reciprocal and two square roots a
+// shell where the general walk takes divisions, and the arc sine of the small angle of a
+// shell by its series (x <= 0.01: the omitted term is below 4e-18 of it). The number of
+// shells is known beforehand; false, and the sums void, where the ray turns or is reflected
+// in one of them.
+__device__ inline bool shell_descent_f64(const double2* __restrict__ nd, const float4* __restrict__ lay, double dh,
+                                         int n_layers, double h_obs, double Re, double h0, double c0, Walk64& w) {
+  const double s0 = sqrt_f64(fmax((1.0 - c0) * (1.0 + c0), 1e-200));
+  int i = min((int)(h0 / dh), n_layers - 1);
+  const int obs = (int)floor(h_obs / dh);
+  const double A = Re + h0, As0 = A * s0;
+  const double Ac1 = A * (c0 * c0 / (1.0 + s0));
+  const double d0 = nd[i].x;
+  w.across = w.len = w.opt = w.tR = w.tA = 0.0;
+  if (!(c0 > 0.0) || i < obs) return false;
+  bool down = true;
+  double ra = A, ha = 0.0;  // ha, hb: heights relative to the start
+  auto shell = [&](int k, double hb_abs) {
+    const double2 n = nd[k];
+    const float4 L = lay[k];
+    const double br = fma(As0 * (n.x - d0), n.y, Ac1);
+    const double rb = Re + hb_abs, hb = hb_abs - h0;
+    const double Da = br + ha, Db = br + hb;
+    const double rca = sqrt_f64(fmax(Da * fma(2.0, ra, -Da), 1e-200)), rcb = sqrt_f64(Db * fma(2.0, rb, -Db));
+    const double rr = ra * rb;
+    const double q = (ha - hb) * (ra + rb) * rcp_f64((rca + rcb) * rr);
+    const double ell = q * rr, x = (ra - Da) * q, x2 = x * x;
+    down = down && Da >= 0.0 && Db > 0.0 && x < 0.01;
+    w.across += fma(x * x2, fma(x2, fma(x2, 15.0 / 336.0, 3.0 / 40.0), 1.0 / 6.0), x);
+    w.len += ell;
+    w.opt = fma(n.x, ell, w.opt);
+    w.tR = fma((double)L.z, ell, w.tR);
+    w.tA = fma((double)L.w, ell, w.tA);
+    ha = hb;
+    ra = rb;
+  };
+#pragma unroll 2
+  for (; i > obs; --i) shell(i, i * dh);
+  shell(obs, h_obs);
+  return down;
+}
+
 // Straight chord from height h0 at local zenith cosine c0 to the sphere R + h_obs,
 // cancellation-free root, and the central angle it sweeps.
 __device__ inline void chord_f64(double Re, double h_obs, double h0, double c0, double& len, double& psi) {
