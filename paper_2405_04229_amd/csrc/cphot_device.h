@@ -476,6 +476,58 @@ __device__ __forceinline__ void curved_walk(const float4* __restrict__ lay, floa
   double psi = 0.0;
   bool down = mu < 0.f;
   int arrived = 0;
+  if constexpr (!NEED_TIME) {
+    // Without the sums along rays that do not arrive: whether a ray passes the lower
+    // boundary of a shell depends on the shell alone (D there, and D just below it), so
+    // one that turns round or is reflected there once never arrives, and its way back up,
+    // or up and down between two boundaries, need not be followed. A wave's walk was as
+    // long as the longest such way, up to 800 shells, and a third of the step's time, most
+    // of it uneven between blocks: inclined shower of 1e7 segments 14.6 -> 11.9 ms; of 1e6
+    // with the table behind which the walk stands 2.27 -> 1.36 ms, with the network 3.2 -> 2.3.
+    while (!down) {  // upward at the start: up to the shell that reflects it
+      const float4 L = lay[i];
+      const float br = bracket(L.x, L.y);
+      const float ra = Rf + h;
+      const float Da = fmaf(A, br, h - h0);
+      const float rca = sqrt_fast(fmaxf(Da * (2.0f * ra - Da), 0.f));
+      const float ho = (float)(i + 1) * dh;
+      const float ro = Rf + ho;
+      const float Do = fmaf(A, br, ho - h0);
+      const float rco = sqrt_fast(fmaxf(Do * (2.0f * ro - Do), 0.f));
+      const float ell = (ho - h) * (twoR + ho + h) * rcp_fast(rco + rca);
+      const float x = (ra - Da) * ell * rcp_fast(ra * ro);
+      tau = fmaf(fmaf(L.z, sp.x, L.w * sp.y), ell, tau);
+      psi += (double)fmaf(x * x * (1.0f / 6.0f), x, x);
+      h = ho;
+      if (i + 1 >= n_layers) break;  // left the atmosphere
+      const float4 Lt = lay[i + 1];
+      down = !(fmaf(A, bracket(Lt.x, Lt.y), h - h0) > 0.f);
+      if (!down) ++i;
+    }
+    if (down) {
+      float4 L = lay[i];
+      float br = bracket(L.x, L.y), Da = fmaf(A, br, h - h0), ra = Rf + h;
+      for (bool go = true; go; --i) {
+        const bool last = i <= obs;
+        const float hb = last ? h_obs : (float)i * dh;
+        const float eb = hb - h0;
+        const float Db = fmaf(A, br, eb);
+        const float rb = Rf + hb;
+        const float rca = sqrt_fast(fmaxf(Da * (2.0f * ra - Da), 0.f)), rcb = sqrt_fast(Db * (2.0f * rb - Db));
+        const float ell = (h - hb) * (twoR + h + hb) * rcp_fast(rca + rcb);
+        const float x = (ra - Da) * ell * rcp_fast(ra * rb);
+        tau = fmaf(fmaf(L.z, sp.x, L.w * sp.y), ell, tau);
+        psi += (double)fmaf(x * x * (1.0f / 6.0f), x, x);
+        L = lay[max(i - 1, 0)];
+        br = bracket(L.x, L.y);
+        Da = fmaf(A, br, eb);
+        h = hb;
+        ra = rb;
+        arrived = last && Db > 0.f;
+        go = !last && Db > 0.f && Da > 0.f;
+      }
+    }
+  } else
   for (int iter = 0; iter < 8 * n_layers; ++iter) {
     const float4 L = lay[i];
     const float br = bracket(L.x, L.y);
