@@ -457,10 +457,13 @@ void grow_window(int& w, int& h, int nx, int ny, size_t area) {
 // 1e4 segments straight 129 71 44 30 23; 1e5 layered 137 78 70 69 82; 4.3e5 in 66 showers
 // straight 435 288 251 260 320, in bunches of 5 136 109 115 138 201; 4e5 curved 1296 1274
 // 1115 1113 1163; 1e6 on spheres in bunches of 5 139 158 203 287 463.
+double rounds_per_tile(const cphot_detector* det) {
+  const double r = 40.0 / det->bunch;
+  return (det->cuts & CPHOT_CUT_TRACK) || det->reduction ? 0.25 * r : r;
+}
+
 int work_shift(const cphot_detector* det, int64_t tiles, int64_t fill) {
-  double r = 40.0 / det->bunch;
-  if ((det->cuts & CPHOT_CUT_TRACK) || det->reduction) r *= 0.25;
-  const double x = 0.45 * r * (double)fill / (double)std::max<int64_t>(tiles, 1);
+  const double x = 0.45 * rounds_per_tile(det) * (double)fill / (double)std::max<int64_t>(tiles, 1);
   return x > 1.0 ? std::min(4, (int)std::lround(0.5 * std::log2(x))) : 0;
 }
 
@@ -562,6 +565,21 @@ int choose_shape(const cphot_detector* det, cphot::KParams& p, int mode, LaunchS
   if (mode == cphot::MODE_COUNTS) g = std::min<int64_t>((p.n + 255) / 256, det->grid_blocks > 0 ? det->grid_blocks : cus * 8);
   else if (g > most) g = most;
   if (g < 1) g = 1;
+  p.taper = 0.f;
+  p.tail_units = 0;
+  if (p.hist_words) {
+    // More blocks than run at a time: the later ones, which start one by one as others end,
+    // take less, so that the CUs end together. Step of 1e7 curved segments on twice the
+    // resident blocks for a taper of 0, 0.3, 0.5, 0.6, 0.8: 11.75 11.24 10.94 10.99 11.59 ms;
+    // 3e6 segments of 16 showers 1188 1122 1087 1076 1079 us. Nothing to gain where all run
+    // at once (1e6 segments on spheres 135 137 132 137 139 us).
+    p.taper = (float)(0.55 * std::min(1.0, std::max(0.0, (double)g / (double)(cus * per_cu) - 1.0)));
+    // A block ends with its last wave: halving the last units pays where a unit is many
+    // rounds long. Half a unit per wave: the 3e6 segments 1078 -> 1036 us, 1e6 curved segments
+    // with the table 1158 -> 1128 us; more or smaller parts change little. On units of few
+    // rounds the repeated set-up costs more (spheres 129 -> 131 us, 1e4 segments 24 -> 26 us).
+    if (rounds_per_tile(det) >= 16 << p.sub_shift) p.tail_units = waves / 2;
+  }
   s.block = bs;
   s.grid = (int)g;
   s.lds = (size_t)p.hist_words * 4;

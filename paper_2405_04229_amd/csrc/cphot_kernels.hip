@@ -1122,14 +1122,20 @@ __global__ __launch_bounds__(BS, (kMinWaves<BS, TRANSPORT>)) void k_propagate(KP
 
   // Units of work: a tile of 64 segments, or with sub_shift one of the 2^sub_shift equal
   // shares of its record rounds. With an LDS histogram the block walks a contiguous range
-  // of them, one run per shower; its waves draw units from the run as they finish.
-  // Without, the waves of the grid take units in turn.
-  const int sub = p.sub_shift;
-  const int64_t n_units = ((p.n + 63) >> 6) << sub;
+  // of them, one run per shower; its waves draw units from the run as they finish, the
+  // last ones of a run in halves, and the ranges fall linearly with the block index where
+  // more blocks are launched than run at a time. Without, the waves of the grid take units
+  // in turn.
+  const int64_t n_units = ((p.n + 63) >> 6) << p.sub_shift;
   int64_t u_first = 0, u_end = n_units;
   if (n_hist) {
-    u_first = (int64_t)blockIdx.x * n_units / gridDim.x;
-    u_end = ((int64_t)blockIdx.x + 1) * n_units / gridDim.x;
+    const KParams& p = fresh_params();
+    auto edge = [&](uint32_t b) {
+      const double x = (double)b / (double)gridDim.x;
+      return (int64_t)((double)n_units * (x + (double)p.taper * x * (1.0 - x)));
+    };
+    u_first = edge(blockIdx.x);
+    u_end = blockIdx.x + 1 == gridDim.x ? n_units : edge(blockIdx.x + 1);
   }
   int win_sh = -1;
   Window win = {0, 0, 0, 0};
@@ -1137,8 +1143,8 @@ __global__ __launch_bounds__(BS, (kMinWaves<BS, TRANSPORT>)) void k_propagate(KP
     run_end = u_end;
     if (n_hist) {
       const KParams& p = fresh_params();
-      const int sh = shower_of(p, (run >> sub) << 6);
-      if (sh + 1 < p.n_showers) run_end = min(u_end, ((p.offsets[sh + 1] + 63) >> 6) << sub);
+      const int sh = shower_of(p, (run >> p.sub_shift) << 6);
+      if (sh + 1 < p.n_showers) run_end = min(u_end, ((p.offsets[sh + 1] + 63) >> 6) << p.sub_shift);
       if (run != u_first) {
         __syncthreads();
         flush_window<BS, DETECTOR>(p, s_hist, win, win_sh);
@@ -1153,16 +1159,28 @@ __global__ __launch_bounds__(BS, (kMinWaves<BS, TRANSPORT>)) void k_propagate(KP
       __syncthreads();
     }
     for (int64_t turn = (int64_t)blockIdx.x * kWaves + (tid >> 6);; turn += (int64_t)gridDim.x * kWaves) {
+      const KParams& p = fresh_params();
       int64_t unit = turn;
+      uint32_t half = 2;  // 0, 1: this half of the unit's rounds; 2: all
       if (n_hist) {
         uint32_t at = 0;
         if (lane == 0) at = atomicAdd(&s_next, 1u);
-        unit = run + (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+        const uint32_t n_run = (uint32_t)(run_end - run), whole = n_run - min((uint32_t)p.tail_units, n_run);
+        if (at >= whole) {
+          half = (at - whole) & 1u;
+          at = whole + ((at - whole) >> 1);
+        }
+        unit = run + at;
       }
       if (unit >= run_end) break;
-      const int64_t tile = unit >> sub;
-      const uint32_t share = (uint32_t)unit & ((1u << sub) - 1u);
-      const KParams& p = fresh_params();
+      const int64_t tile = unit >> p.sub_shift;
+      int sub = p.sub_shift;
+      uint32_t share = (uint32_t)unit & ((1u << sub) - 1u);
+      if (half < 2u) {
+        share = 2u * share + half;
+        ++sub;
+      }
       // ---- 1. the tile's segments, one per lane
       const int64_t i = (tile << 6) + lane;
       uint32_t n_ch = 0, n_fl = 0;

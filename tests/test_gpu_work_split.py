@@ -95,3 +95,23 @@ def test_records_of_shared_tiles(transport):
         states = np.bincount(r["state"], minlength=4)
         assert cnt[3] == total and cnt[4] == states[1] and cnt[5] == states[2]
         assert cnt[6] == states[3] and cnt[7] == states[0]
+
+
+@pytest.mark.parametrize("transport,detector,bunch", [("straight", "grid", 1), ("curved", "grid", 1),
+                                                      ("layered", "spheres", 5)])
+@pytest.mark.parametrize("sizes", [(70_001,), (20_000, 64, 5, 30_000)])
+def test_more_blocks_than_fit(transport, detector, bunch, sizes):
+    """Blocks' ranges that fall with the block index, and runs whose last units are halved:
+    every record once, whatever the number of blocks."""
+    atm = cphot.Atmosphere(**cases.ATMO_LAYERED)
+    kw = dict(transport=transport, spectrum="frank_tamm", seed=9, bunch=bunch, detector=detector)
+    kw.update(dict(nx=100, ny=100, cell=10.0) if detector == "grid" else dict(snx=10, sny=10, pitch=150.0, radius=6.0))
+    seg, offs, geom = _showers(sizes, 50.0, None)
+    S = cphot.make_segments(*cphot.upload(seg, geom, offs))
+    cells = 10_000 if detector == "grid" else 100
+    ref = _run(S, cphot.make_detector(atm, **kw, block_size=128, lds_hist=0), len(sizes), cells, torch.int64)
+    for block in (128, 256, 512):
+        for blocks in (1, 7, 1000, 2100, 10**6):
+            got = _run(S, cphot.make_detector(atm, **kw, block_size=block, grid_blocks=blocks, lds_hist=1), len(sizes),
+                       cells, torch.int64)
+            assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1]), (block, blocks)
