@@ -458,7 +458,8 @@ struct ShowerState {
 // transport every lane of the wave must call this together (`valid` marks the
 // lanes that carry a real record); the network is evaluated before any lane
 // leaves. H: the arguments of the common path (Hot, or KParams where few records go).
-template <int TRANSPORT, int DETECTOR, bool NEED_TIME, bool EXT, class K>
+// ROWS: list mode, where every record's arrival time is written, not only a binned one's.
+template <int TRANSPORT, int DETECTOR, bool NEED_TIME, bool ROWS, bool EXT, class K>
 __device__ __forceinline__ void trace(const K& H, const KParams& p, const Tables& T, const SegState& g,
                                       const ShowerState& S, bool fl, uint32_t kk, bool valid, Photon& o) {
   const float4* s_lay = T.lay;
@@ -769,6 +770,7 @@ __device__ __forceinline__ void trace(const K& H, const KParams& p, const Tables
   float vx, vy, vz;  // direction of the final leg
   float tau = 0.f, geo = 0.f, opt = 0.f;
   float last_delta = 0.f, last_ext = 0.f;
+  bool series = false;  // the path sums came from the closed forms, without those of the time
   if constexpr (TRANSPORT != CPHOT_TRANSPORT_STRAIGHT) {
     if (TRANSPORT == CPHOT_TRANSPORT_LAYERED || !use_mlp) {
       if constexpr (TRANSPORT == CPHOT_TRANSPORT_SURROGATE || TRANSPORT == CPHOT_TRANSPORT_TABLE) {
@@ -778,9 +780,10 @@ __device__ __forceinline__ void trace(const K& H, const KParams& p, const Tables
       LayerWalk lw;
       const int j0 = min((int)(Pz * H.inv_dh), H.n_layers - 1);
       // closed-form sums where the series holds, the crossing loop elsewhere
-      if (j0 > H.obs_layer && fmaf(ux, ux, uy * uy) <= H.series_tmax * (uz * uz))
-        layer_series<NEED_TIME>(s_lay, H.moments, s_lam[kb], H.dh, j0, H.obs_layer, Px, Py, Pz, ux, uy, uz, axx,
-                                axy, axz, lw);
+      series = j0 > H.obs_layer && fmaf(ux, ux, uy * uy) <= H.series_tmax * (uz * uz);
+      if (series)
+        layer_series<NEED_TIME && ROWS>(s_lay, H.moments, s_lam[kb], H.dh, j0, H.obs_layer, Px, Py, Pz, ux, uy, uz,
+                                        axx, axy, axz, lw);
       else
         layer_walk<NEED_TIME>(s_lay, s_lam[kb], H.dh, j0, H.obs_layer, Px, Py, Pz, ux, uy, uz, axx, axy,
                                      axz, lw);
@@ -873,18 +876,14 @@ __device__ __forceinline__ void trace(const K& H, const KParams& p, const Tables
     }
   }
   const float ex = fmaf(s_end, vx, x), ey = fmaf(s_end, vy, y), ez = fmaf(s_end, vz, z);
+  float inv_uz = 0.f, Xe = 0.f, X_end = 0.f;
   if constexpr (TRANSPORT != CPHOT_TRANSPORT_STRAIGHT) {
     tau = fmaf(last_ext, s_end, tau);
-    if constexpr (NEED_TIME) {
-      const float gx = vx - axx, gy = vy - axy, gz = vz - axz;
-      geo = fmaf(s_end, 0.5f * (gx * gx + gy * gy + gz * gz), geo);
-      opt = fmaf(last_delta, s_end, opt);
-    }
   } else {
     // straight line in a planar atmosphere: closed forms over the height span
-    const float inv_uz = -1.0f / vz;  // 1/|u_z|
-    const float Xe = fmaf(f, g.dX, g.q2.w);
-    float X_end = p.X_obs;
+    inv_uz = -1.0f / vz;  // 1/|u_z|
+    Xe = fmaf(f, g.dX, g.q2.w);
+    X_end = p.X_obs;
     if constexpr (DETECTOR == CPHOT_DETECTOR_SPHERES) {
       if (p.profile == CPHOT_PROFILE_LINSLEY5) X_end = depth_f(*s_k, ez);
     }
@@ -897,17 +896,34 @@ __device__ __forceinline__ void trace(const K& H, const KParams& p, const Tables
       const float taua = p.aer_tau350 * __powf(lam * (1.0f / 350.0f), -p.aer_ang);
       tau = fmaf(taua * (__expf(-ez * p.aer_inv_h) - __expf(-Pz * p.aer_inv_h)), inv_uz, tau);
     }
-    if constexpr (NEED_TIME) {
-      const float gx = vx - axx, gy = vy - axy, gz = vz - axz;
-      geo = s_end * 0.5f * (gx * gx + gy * gy + gz * gz);
-      opt = opt_integral(p, ez, Pz, X_end, Xe) * inv_uz;
-    }
   }
+  // Delay after the plane front. Few records are binned (of the telescope array's 1 in
+  // 170), so its sums are formed where they are used, in a third of the waves (1e6
+  // segments 130 -> 127 us).
+  auto delay = [&]() {
+    const float gx = vx - axx, gy = vy - axy, gz = vz - axz;
+    const float g2 = gx * gx + gy * gy + gz * gz;
+    if constexpr (TRANSPORT == CPHOT_TRANSPORT_STRAIGHT) {
+      geo = s_end * 0.5f * g2;
+      opt = opt_integral(p, ez, Pz, X_end, Xe) * inv_uz;
+    } else {
+      if (!ROWS && series) {
+        LayerWalk lw;
+        layer_series<true>(s_lay, H.moments, s_lam[kb], H.dh, min((int)(Pz * H.inv_dh), H.n_layers - 1), H.obs_layer, Px,
+                           Py, Pz, ux, uy, uz, axx, axy, axz, lw);
+        geo = lw.geo;
+        opt = lw.opt;
+      }
+      geo = fmaf(s_end, 0.5f * g2, geo);
+      opt = fmaf(last_delta, s_end, opt);
+    }
+    return (geo + opt) * (1.0f / kCmPerNs);
+  };
   o.x = ex;
   o.y = ey;
   o.z = ez;
   o.tau = tau;
-  if constexpr (NEED_TIME) o.t = (geo + opt) * (1.0f / kCmPerNs);
+  if constexpr (NEED_TIME && ROWS) o.t = delay();
   if (!(u3 < survival_threshold(s_eff, tau, kb, g.inv_q))) {
     o.state = kStateAbsorbed;
     return;
@@ -920,7 +936,7 @@ __device__ __forceinline__ void trace(const K& H, const KParams& p, const Tables
   o.bin = bin;
   if constexpr (DETECTOR == CPHOT_DETECTOR_SPHERES) {
     if (H.n_t > 0) {
-      const float tb = floorf(o.t * H.inv_dt);
+      const float tb = floorf((ROWS ? o.t : delay()) * H.inv_dt);
       o.tbin = tb < 0.f ? 0 : (tb >= (float)H.n_t ? H.n_t : (int)tb);
     }
   }
@@ -1418,7 +1434,7 @@ __global__ __launch_bounds__(BS, (kMinWaves<BS, TRANSPORT>)) void k_propagate(KP
           if (kMlp || valid) {
             SegState g;
             load_slot(s, g);
-            trace<TRANSPORT, DETECTOR, kTime, EXT>(H, pr, T, g, S, fl, kk, valid, ph);
+            trace<TRANSPORT, DETECTOR, kTime, kRecords, EXT>(H, pr, T, g, S, fl, kk, valid, ph);
             if (!kRecords && valid && (!kDefer || ph.state != kStateDeferred)) consume(pr, ph);
           }
           if constexpr (kRecords) write_rows(pr, ph, s, fl, kk, valid && (!kDefer || ph.state != kStateDeferred));
@@ -1458,7 +1474,7 @@ __global__ __launch_bounds__(BS, (kMinWaves<BS, TRANSPORT>)) void k_propagate(KP
               if (mine) {
                 SegState g;
                 load_slot(qs, g);
-                trace<decltype(transport)::value, DETECTOR, kTime, EXT>(pq, pq, T, g, S, qfl, qk, true, pe);
+                trace<decltype(transport)::value, DETECTOR, kTime, kRecords, EXT>(pq, pq, T, g, S, qfl, qk, true, pe);
               }
               const bool done_with = pe.state != kStateDeferred;
               if constexpr (kRecords) write_rows(pq, pe, qs, qfl, qk, done_with);
