@@ -441,12 +441,15 @@ void grow_window(int& w, int& h, int nx, int ny, size_t area) {
 // it fits, else the rectangle around the core where most photons land; each block walks a
 // contiguous range of segments and flushes its window when the shower changes.
 //
-// The library's own shape on a ground grid is one block per CU, as large as the registers
+// The library's own shape is one block per CU, as large as the registers
 // allow (16 waves, 12 with the network), because its waves share one window: the window
 // takes all the LDS that the segment slots leave (about 22,000 cells, where four blocks of
 // 256 have 4,800 each), one flush serves 16 waves, and every CU ends with its last wave.
 // Against one block of 256 per 256 segments with device atomics: inclined shower of 1e6
 // segments with the correction table 7.7 -> 2.2 ms, with the network 8.2 -> 3.2 ms.
+// On spheres the same block replaces four of 256 per CU, of which the first ran a third
+// faster than the last (a SIMD prefers its oldest wave) while its waves draw from one run:
+// 1e6 segments 130 -> 117 us, 3e5 with cuts and reduction 39 -> 31 us.
 //
 // A tile's record rounds can be shared by 2^k units of work (work_shift). More units
 // balance the waves at the end of a launch and fill the chip when tiles are few; each
@@ -473,8 +476,8 @@ int choose_shape(const cphot_detector* det, cphot::KParams& p, int mode, LaunchS
   if (det->hist_window < 0 || det->hist_window_h < 0)
     return fail(CPHOT_ERR_INVALID_ARG, "hist_window and hist_window_h must be >= 0");
   const bool propagate = mode == cphot::MODE_PROPAGATE, on_grid = p.detector == CPHOT_DETECTOR_GRID;
-  const bool own = propagate && on_grid && det->block_size == 0 && det->grid_blocks <= 0 && det->lds_hist != 0 &&
-                   det->hist_window == 0;
+  const bool own = propagate && det->block_size == 0 && det->grid_blocks <= 0 &&
+                   (on_grid ? det->lds_hist != 0 && det->hist_window == 0 : det->lds_hist < 0);
   const int bs = own ? cphot::kBigBlock : det->block_size ? det->block_size : 256;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) dev = 0;

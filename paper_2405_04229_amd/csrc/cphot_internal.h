@@ -174,7 +174,7 @@ TableView table_view(const cphot_table* t);
 const cphot_atmosphere* table_atmosphere(const cphot_table* t);
 double table_h_obs(const cphot_table* t);
 
-// The library's own block size on ground grids: one block per CU (kBig threads).
+// The library's own block size: one block per CU (kBig threads).
 constexpr int kBigBlock = 1024;
 hipError_t launch_propagate(const KParams& p, int mode, int block_size, int grid_blocks, size_t lds_hist_bytes,
                             hipStream_t stream);

@@ -1577,7 +1577,7 @@ KernelInfo info_one() {
 }  // namespace
 
 // Each block size is compiled by itself (CPHOT_BLOCK), so that they build side by side.
-// The large size serves the library's own choice on ground grids: 1024 threads, or 768
+// The large size serves the library's own choice: 1024 threads, or 768
 // for the network kernels, whose registers allow three waves per SIMD.
 #if CPHOT_BLOCK == 1024
 template <int T>
@@ -1587,19 +1587,25 @@ template <>
 hipError_t launch_block<1024>(const KParams& p, int mode, dim3 grid, size_t lds, hipStream_t s) {
   (void)mode;
   const bool ext = p.poisson || p.spectrum == CPHOT_SPECTRUM_DISPERSIVE;
-#define CPHOT_BIG(T) \
-  case T: \
-    return ext ? launch_one<kBig<T>, T, 0, MODE_PROPAGATE, true>(p, grid, lds, s) \
-               : launch_one<kBig<T>, T, 0, MODE_PROPAGATE, false>(p, grid, lds, s);
+#define CPHOT_BIG(T, D) \
+  return ext ? launch_one<kBig<T>, T, D, MODE_PROPAGATE, true>(p, grid, lds, s) \
+             : launch_one<kBig<T>, T, D, MODE_PROPAGATE, false>(p, grid, lds, s);
+  if (p.detector == CPHOT_DETECTOR_SPHERES) switch (p.transport) {
+    case CPHOT_TRANSPORT_STRAIGHT: CPHOT_BIG(CPHOT_TRANSPORT_STRAIGHT, 1)
+    case CPHOT_TRANSPORT_LAYERED: CPHOT_BIG(CPHOT_TRANSPORT_LAYERED, 1)
+    case CPHOT_TRANSPORT_SURROGATE: CPHOT_BIG(CPHOT_TRANSPORT_SURROGATE, 1)
+    case CPHOT_TRANSPORT_TABLE: CPHOT_BIG(CPHOT_TRANSPORT_TABLE, 1)
+    default: return hipErrorInvalidValue;
+  }
   switch (p.transport) {
-    CPHOT_BIG(CPHOT_TRANSPORT_STRAIGHT)
-    CPHOT_BIG(CPHOT_TRANSPORT_LAYERED)
-    CPHOT_BIG(CPHOT_TRANSPORT_SURROGATE)
-    CPHOT_BIG(CPHOT_TRANSPORT_CURVED)
-    CPHOT_BIG(CPHOT_TRANSPORT_TABLE)
-    CPHOT_BIG(kTransportCurvedWalk)
-    CPHOT_BIG(kTransportCurvedTable)
-    CPHOT_BIG(kTransportCurvedSurrogate)
+    case CPHOT_TRANSPORT_STRAIGHT: CPHOT_BIG(CPHOT_TRANSPORT_STRAIGHT, 0)
+    case CPHOT_TRANSPORT_LAYERED: CPHOT_BIG(CPHOT_TRANSPORT_LAYERED, 0)
+    case CPHOT_TRANSPORT_SURROGATE: CPHOT_BIG(CPHOT_TRANSPORT_SURROGATE, 0)
+    case CPHOT_TRANSPORT_CURVED: CPHOT_BIG(CPHOT_TRANSPORT_CURVED, 0)
+    case CPHOT_TRANSPORT_TABLE: CPHOT_BIG(CPHOT_TRANSPORT_TABLE, 0)
+    case kTransportCurvedWalk: CPHOT_BIG(kTransportCurvedWalk, 0)
+    case kTransportCurvedTable: CPHOT_BIG(kTransportCurvedTable, 0)
+    case kTransportCurvedSurrogate: CPHOT_BIG(kTransportCurvedSurrogate, 0)
     default: return hipErrorInvalidValue;
   }
 #undef CPHOT_BIG
@@ -1607,6 +1613,12 @@ hipError_t launch_block<1024>(const KParams& p, int mode, dim3 grid, size_t lds,
 
 template <>
 KernelInfo info_block<1024>(const KParams& p) {
+  if (p.detector == CPHOT_DETECTOR_SPHERES) switch (p.transport) {
+    case CPHOT_TRANSPORT_STRAIGHT: return info_one<1024, CPHOT_TRANSPORT_STRAIGHT, 1>();
+    case CPHOT_TRANSPORT_LAYERED: return info_one<1024, CPHOT_TRANSPORT_LAYERED, 1>();
+    case CPHOT_TRANSPORT_TABLE: return info_one<1024, CPHOT_TRANSPORT_TABLE, 1>();
+    default: return info_one<768, CPHOT_TRANSPORT_SURROGATE, 1>();
+  }
   switch (p.transport) {
     case CPHOT_TRANSPORT_STRAIGHT: return info_one<1024, CPHOT_TRANSPORT_STRAIGHT, 0>();
     case CPHOT_TRANSPORT_LAYERED: return info_one<1024, CPHOT_TRANSPORT_LAYERED, 0>();

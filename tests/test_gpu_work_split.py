@@ -115,3 +115,31 @@ def test_more_blocks_than_fit(transport, detector, bunch, sizes):
             got = _run(S, cphot.make_detector(atm, **kw, block_size=block, grid_blocks=blocks, lds_hist=1), len(sizes),
                        cells, torch.int64)
             assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1]), (block, blocks)
+
+
+@pytest.mark.parametrize("transport", ["straight", "layered", "table", "surrogate"])
+@pytest.mark.parametrize("side", [10, 250])
+def test_own_shape_on_spheres(transport, side):
+    """Sphere and time counts: an array that fits in LDS and one of 62,500 spheres, which
+    does not; integer counts, equal in every bin."""
+    atm = cphot.Atmosphere(**cases.ATMO_LAYERED)
+    kw = dict(transport=transport, spectrum="frank_tamm", seed=9, bunch=2, detector="spheres", snx=side, sny=side,
+              pitch=1500.0 / side, radius=300.0 / side, n_t=64, dt=2.0)
+    if transport == "table":
+        kw["table"] = cphot.Table(atm, 2200.0)
+    if transport == "surrogate":
+        lo, hi = np.array(W.SURROGATE_LO), np.array(W.SURROGATE_HI)
+        kw["surrogate"] = cphot.Surrogate(lo, hi, max_batch=64)
+        kw["surrogate"].set_params(norm=np.array([*lo, *hi, *(2.0 / (hi - lo)), 0, 0, 0, 0, -1e-5, 1e-5, 1, 1e-5, 1e-5]))
+    for sizes in ((1,), (65,), (20_000,), (40, 3, 1, 500, 77)):
+        seg, offs, geom = _showers(sizes, 30.0, None)
+        S = cphot.make_segments(*cphot.upload(seg, geom, offs))
+        out = []
+        for shape in (dict(), dict(block_size=128, lds_hist=0)):
+            bins = torch.zeros(len(sizes) * side * side, dtype=torch.int64, device="cuda")
+            times = torch.zeros(len(sizes) * side * side * 65, dtype=torch.int32, device="cuda")
+            cnt = torch.zeros(cphot.NCOUNTERS, dtype=torch.int64, device="cuda")
+            cphot.propagate(S, cphot.make_detector(atm, **kw, **shape), bins, times, cnt)
+            out.append((bins, times, cnt))
+        assert all(torch.equal(a, b) for a, b in zip(*out)), sizes
+        assert len(sizes) == 1 or int(out[0][2][7]) > 0
