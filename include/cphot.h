@@ -398,7 +398,7 @@ void cphot_step_destroy(cphot_step* step);
 /* Result of cphot_autotune: the launch shape to put into cphot_detector. */
 typedef struct {
   int32_t block_size;
-  int32_t grid_blocks;   /* 0 = one block per tile */
+  int32_t grid_blocks;   /* 0 = the library's choice */
   int32_t lds_hist;
   int32_t bunch;
   int32_t hist_window;   /* LDS window width in cells (0 with lds_hist 0) */

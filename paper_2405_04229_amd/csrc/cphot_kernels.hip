@@ -1108,7 +1108,7 @@ __global__ __launch_bounds__(BS, (kMinWaves<BS, TRANSPORT>)) void k_propagate(KP
   // serialise on its cache line.
   extern __shared__ uint32_t s_hist[];
   __shared__ unsigned long long s_since;  // records counted in the window since the last flush
-  __shared__ uint32_t s_next;             // next tile of the block's run, from its first
+  __shared__ uint32_t s_next;             // next unit of the block's run, from its first
   const int n_hist = MODE == MODE_PROPAGATE ? p.hist_words : 0;
   const int tid = threadIdx.x, lane = tid & 63, wbase = tid & ~63;
 
