@@ -70,12 +70,12 @@ METRIC = "photons propagated/s, exact vs MLP surrogate, at <=1% per-bin density 
 KERNEL_SOURCES = ("cphot_kernels.hip", "cphot_device.h", "cphot_internal.h", "cphot_mlp.h")
 MEASURED = {
     # profiles/k_propagate_curved_inclined_1e7.md: mean of the six launches of the timed step
-    "inclined_curved": {"sha": "66494fdc41f0885c", "shape": [256, 2048, 1, 90, 45, 1, 1],
-                        "valu_insts": 8.553303493e9, "hbm_bytes": (176773.29 * 2.0 + 576439.55 * 1.0) * 1024,
+    "inclined_curved": {"sha": "930855b3c4548d89", "shape": [512, 2048, 1, 143, 73, 0, 0],
+                        "valu_insts": 7.060329e9, "hbm_bytes": (176770.4 * 2.0 + 436186.0 * 1.0) * 1024,
                         "profile": "profiles/k_propagate_curved_inclined_1e7.md"},
     # profiles/k_propagate_telescope_1e6.md: mean of the six launches of the timed step
-    "telescope_layered": {"sha": "66494fdc41f0885c", "shape": [256, 1024, 1, 0, 0, 0, 0],
-                          "valu_insts": 7.3883896e7, "hbm_bytes": (16270.24 * 2.0 + 288.0 * 1.0) * 1024,
+    "telescope_layered": {"sha": "930855b3c4548d89", "shape": [256, 1024, 1, 0, 0, 0, 0],
+                          "valu_insts": 6.62356e7, "hbm_bytes": (16242.0 * 2.0 + 288.0 * 1.0) * 1024,
                           "profile": "profiles/k_propagate_telescope_1e6.md"},
 }
 
@@ -865,24 +865,23 @@ def bench_batched(torch, cphot, W, args, stream):
 
 
 def block_balance(torch, cphot, S, det, n, tune):
-    """Records per block of the persistent grid's static partition (each block
-    walks a contiguous range of tiles), from the per-segment record counts."""
+    """How uneven the light is between equal contiguous ranges of tiles, one per
+    block of the tuned grid, from the per-segment record counts."""
     counts = torch.zeros(n, dtype=torch.int32, device="cuda")
     cphot.segment_counts(S, det, counts)
     torch.cuda.synchronize()
     c = counts.cpu().numpy().astype(np.int64)
-    bs = int(tune["block_size"])
-    tiles = np.add.reduceat(c, np.arange(0, n, bs))
+    tiles = np.add.reduceat(c, np.arange(0, n, 64))  # a tile is a wave's 64 segments
     nt = len(tiles)
-    grid = min(int(tune["grid_blocks"]), nt)  # the library clamps the grid to the tile count
+    grid = min(int(tune["grid_blocks"]), nt)
     first = (np.arange(grid, dtype=np.int64) * nt) // grid
     per_block = np.add.reduceat(tiles, first)
     mean = float(per_block.mean())
     return {"blocks": grid, "tiles": nt, "records_per_block_mean": mean,
             "records_per_block_max_over_mean": float(per_block.max()) / mean,
             "records_per_block_cv": float(per_block.std()) / mean,
-            "note": "static contiguous tile ranges; more blocks than fit on the chip at once, so the "
-                    "dispatcher starts the later ones as earlier ones finish"}
+            "note": "equal contiguous ranges; the library's ranges fall with the block index where more "
+                    "blocks are launched than run at a time"}
 
 
 # ------------------------------------------------------------------------------ main
