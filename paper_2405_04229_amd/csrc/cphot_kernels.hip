@@ -1109,7 +1109,10 @@ __global__ __launch_bounds__(BS, (kMinWaves<BS, TRANSPORT>)) void k_propagate(KP
   extern __shared__ uint32_t s_hist[];
   __shared__ unsigned long long s_since;  // records counted in the window since the last flush
   __shared__ uint32_t s_next;             // next unit of the block's run, from its first
-  __shared__ int64_t s_range[2];          // segments of the run's shower
+  // segments of the run's shower (kept where batches run; in the curved kernels the few
+  // registers it takes cost 1 %)
+  constexpr bool kRange = DETECTOR == CPHOT_DETECTOR_GRID && (TRANSPORT == CPHOT_TRANSPORT_STRAIGHT || TRANSPORT == CPHOT_TRANSPORT_LAYERED);
+  __shared__ int64_t s_range[kRange ? 2 : 1];
   const int n_hist = MODE == MODE_PROPAGATE ? p.hist_words : 0;
   const int tid = threadIdx.x, lane = tid & 63, wbase = tid & ~63;
 
@@ -1172,8 +1175,10 @@ __global__ __launch_bounds__(BS, (kMinWaves<BS, TRANSPORT>)) void k_propagate(KP
       if (tid == 0) {
         s_next = 0u;
         s_since = 0ull;
-        s_range[0] = p.n_showers > 1 ? p.offsets[sh] : 0;
-        s_range[1] = sh + 1 < p.n_showers ? p.offsets[sh + 1] : p.n;
+        if constexpr (kRange) {
+          s_range[0] = p.n_showers > 1 ? p.offsets[sh] : 0;
+          s_range[1] = sh + 1 < p.n_showers ? p.offsets[sh + 1] : p.n;
+        }
       }
       __syncthreads();
     }
@@ -1234,8 +1239,8 @@ __global__ __launch_bounds__(BS, (kMinWaves<BS, TRANSPORT>)) void k_propagate(KP
         if (n_ch + n_fl) {
           // nearly always the run's shower; the search is a chain of dependent loads (3e6
           // segments in 16 showers 1,112 us with it for every segment, 1,094 without)
-          if (p.n_showers > 1)
-            sh_of = n_hist && i >= s_range[0] && i < s_range[1] ? (uint32_t)win_sh : (uint32_t)shower_of(p, i);
+          if (kRange && n_hist && i >= s_range[0] && i < s_range[1]) sh_of = (uint32_t)win_sh;
+          else sh_of = (uint32_t)shower_of(p, i);
           float X0 = 0.f;
           if (!kLayers && p.profile == CPHOT_PROFILE_LINSLEY5) {
             X0 = depth_f(s_k, fz0);
