@@ -909,24 +909,43 @@ struct cphot_step {
 
 namespace {
 
-__global__ void k_fill_u32(uint32_t* p, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = 0u;
-}
-
-hipError_t clear_words(void* ptr, int64_t bytes, hipStream_t st) {
-  if (!ptr || bytes <= 0) return hipSuccess;
-  const int64_t n = bytes / 4;
-  const int blocks = (int)std::min<int64_t>((n + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_fill_u32, dim3(blocks), dim3(256), 0, st, (uint32_t*)ptr, n);
-  return hipGetLastError();
+// Clears the outputs of a step in one launch: up to three spans of words, 16 bytes a store.
+// One launch for each span cost the smallest steps as much as the clearing (2e4 segments
+// 38.7 us a replay, 37.0 with one).
+struct ClearSpans {
+  uint32_t* p[3];
+  int64_t n[3];
+};
+__global__ void k_clear(ClearSpans c) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    uint32_t* p = c.p[s];
+    const int64_t n = c.n[s], head = min((int64_t)((0u - (uint32_t)((uintptr_t)p >> 2)) & 3u), n), quads = (n - head) >> 2;
+    uint4* q = reinterpret_cast<uint4*>(p + head);
+    for (int64_t i = t; i < quads; i += step) q[i] = make_uint4(0u, 0u, 0u, 0u);
+    const int64_t rest = head + 4 * quads;  // fewer than four words before and after
+    if (t < head) p[t] = 0u;
+    if (t < n - rest) p[rest + t] = 0u;
+  }
 }
 
 hipError_t clear_outputs(const cphot_bins* out, hipStream_t st) {
-  hipError_t e = clear_words(out->bins, out->bins_capacity * (out->bins_dtype == CPHOT_BINS_U32 ? 4 : 8), st);
-  if (e == hipSuccess) e = clear_words(out->time_hist, out->time_capacity * 4, st);
-  if (e == hipSuccess && out->counters) e = clear_words(out->counters, CPHOT_NCOUNTERS * 8, st);
-  return e;
+  ClearSpans c = {};
+  const int64_t bytes[3] = {out->bins_capacity * (out->bins_dtype == CPHOT_BINS_U32 ? 4 : 8), out->time_capacity * 4,
+                            CPHOT_NCOUNTERS * 8};
+  void* const ptr[3] = {out->bins, out->time_hist, out->counters};
+  int64_t most = 0;
+  for (int s = 0; s < 3; ++s) {
+    if (!ptr[s] || bytes[s] <= 0) continue;
+    c.p[s] = (uint32_t*)ptr[s];
+    c.n[s] = bytes[s] / 4;
+    most = std::max(most, c.n[s]);
+  }
+  if (most == 0) return hipSuccess;
+  const int blocks = (int)std::min<int64_t>((most + 1023) / 1024, 4096);
+  hipLaunchKernelGGL(k_clear, dim3(blocks), dim3(256), 0, st, c);
+  return hipGetLastError();
 }
 
 }  // namespace
