@@ -131,6 +131,7 @@ struct KParams {
   int32_t hist_auto;                   // grid: window area in cells, its sides from the shower axis (0: hist_w x hist_h)
   int32_t sub_shift;                   // the rounds of a tile are shared by 2^sub_shift units of work
   float taper;                         // LDS counts: the blocks' shares fall from 1 + taper to 1 - taper
+  float inv_share4;                    // LDS counts: 4 over the mean units of a block (0: no priorities)
   int32_t tail_units;                  // LDS counts: so many last units of a run are halved
   int32_t hist_w, hist_h;              // window size in cells (x, y)
   int32_t hist_x0, hist_y0;            // window origin in cells

@@ -1191,6 +1191,18 @@ __global__ __launch_bounds__(BS, (kMinWaves<BS, TRANSPORT>)) void k_propagate(KP
         if (lane == 0) at = atomicAdd(&s_next, 1u);
         at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
         const uint32_t n_run = (uint32_t)(run_end - run), whole = n_run - min((uint32_t)p.tail_units, n_run);
+        // A SIMD issues its oldest wave first, and equal blocks of one CU ended a third apart;
+        // the more units a block has left (in quarters of a mean block's), the higher its
+        // waves' priority (telescope array 127 -> 113 us; all blocks above 512 are alone on
+        // their CU).
+        if constexpr (BS <= 512) {
+          const float left = (float)(uint32_t)max((int64_t)0, u_end - run - at) * p.inv_share4;
+          const int rank = __builtin_amdgcn_readfirstlane((int)left);
+          if (rank <= 0) __builtin_amdgcn_s_setprio(0);
+          else if (rank == 1) __builtin_amdgcn_s_setprio(1);
+          else if (rank == 2) __builtin_amdgcn_s_setprio(2);
+          else __builtin_amdgcn_s_setprio(3);
+        }
         if (at >= whole) {
           half = (at - whole) & 1u;
           at = whole + ((at - whole) >> 1);
