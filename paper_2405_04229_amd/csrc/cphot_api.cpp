@@ -527,8 +527,9 @@ int choose_shape(const cphot_detector* det, cphot::KParams& p, int mode, LaunchS
       p.lds_hist = 1;
       p.hist_w = w;
       p.hist_h = h;
-      p.hist_x0 = std::min(std::max((p.nx - w) / 2 + det->hist_window_dx, 0), p.nx - w);
-      p.hist_y0 = std::min(std::max((p.ny - h) / 2 + det->hist_window_dy, 0), p.ny - h);
+      const int dx = std::min(std::max(det->hist_window_dx, -p.nx), p.nx), dy = std::min(std::max(det->hist_window_dy, -p.ny), p.ny);
+      p.hist_x0 = p.hist_auto ? dx : std::min(std::max((p.nx - w) / 2 + dx, 0), p.nx - w);
+      p.hist_y0 = p.hist_auto ? dy : std::min(std::max((p.ny - h) / 2 + dy, 0), p.ny - h);
       p.hist_words = p.hist_auto ? p.hist_auto : w * h;
     } else {
       p.hist_auto = 0;

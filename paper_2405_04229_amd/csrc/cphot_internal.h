@@ -134,7 +134,7 @@ struct KParams {
   float inv_share4;                    // LDS counts: 4 over the mean units of a block (0: no priorities)
   int32_t tail_units;                  // LDS counts: so many last units of a run are halved
   int32_t hist_w, hist_h;              // window size in cells (x, y)
-  int32_t hist_x0, hist_y0;            // window origin in cells
+  int32_t hist_x0, hist_y0;            // window origin in cells (hist_auto: the shift of its centre)
   int32_t hist_tw;                     // spheres: leading time bins of each sphere held in LDS too
   uint32_t* thist;
   unsigned long long* counters;

@@ -993,8 +993,8 @@ struct Window {
 // The window of a shower's grid. The launch gives the rectangle, or only its area
 // (hist_auto): then the sides are in the ratio of the extents of a round spot, cast along
 // the shower axis, on the ground (1 + (axis_x / axis_z)^2 and the same in y, squared), and
-// the rectangle is centred on the grid. Photons of a shower inclined by 60 degrees that
-// miss a square of the same area cost a device atomic each.
+// the rectangle's centre is the grid's plus the caller's shift, inside the grid. Photons of a
+// shower inclined by 60 degrees that miss a square of the same area cost a device atomic each.
 __device__ __forceinline__ Window shower_window(const KParams& p, int sh) {
   Window w = {p.hist_w, p.hist_h, p.hist_x0, p.hist_y0};
   if (p.hist_auto) {
@@ -1008,8 +1008,8 @@ __device__ __forceinline__ Window shower_window(const KParams& p, int sh) {
     if (w.h == p.ny) w.w = min(p.hist_auto / w.h, p.nx);
     w.w = __builtin_amdgcn_readfirstlane(w.w);
     w.h = __builtin_amdgcn_readfirstlane(w.h);
-    w.x0 = (p.nx - w.w) / 2;
-    w.y0 = (p.ny - w.h) / 2;
+    w.x0 = min(max((p.nx - w.w) / 2 + p.hist_x0, 0), p.nx - w.w);
+    w.y0 = min(max((p.ny - w.h) / 2 + p.hist_y0, 0), p.ny - w.h);
   }
   return w;
 }
