@@ -542,7 +542,9 @@ int choose_shape(const cphot_detector* det, cphot::KParams& p, int mode, LaunchS
   // later bins stay global. The time part takes only the LDS that leaves the
   // occupancy the kernel's registers allow.
   if (propagate && !on_grid && det->lds_hist != 0) {
-    const size_t most = lds_share(std::max(1, std::min(per_cu, 8 / waves)));
+    // A block may hold half a CU's LDS, a block of eight waves or more all of it: larger
+    // shares leave less than one wave per SIMD.
+    const size_t most = lds_share(std::max(1, std::min({per_cu, 2, 8 / waves})));
     const size_t room = info.lds < most ? (most - info.lds) / 4 : 0;
     const size_t nsph = (size_t)p.snx * p.sny;
     if (nsph > room) {
@@ -551,6 +553,7 @@ int choose_shape(const cphot_detector* det, cphot::KParams& p, int mode, LaunchS
       p.lds_hist = 1;
       p.hist_w = p.snx;
       p.hist_h = p.sny;
+      while (per_cu > 1 && lds_share(per_cu) < info.lds + nsph * 4) --per_cu;  // blocks that fit together
       const size_t cap = lds_share(per_cu);
       if (p.n_t > 0 && cap > info.lds + nsph * 4) {
         const size_t tb = std::min((cap - info.lds) / 4 - nsph, room - nsph) / nsph;
