@@ -262,13 +262,15 @@ typedef struct {
   int32_t block_size;       /* tuning: threads per block (0 = library choice) */
   int32_t grid_blocks;      /* tuning: blocks of the persistent grid (0 = library choice) */
   int32_t lds_hist;         /* tuning: 1 = privatise the counts in LDS (GRID: the whole grid if it
-                               fits, else a window of it; SPHERES: the whole sphere array, an error
-                               if it does not fit), 0 = global atomics only, -1 = library choice */
-  int32_t hist_window;      /* tuning: GRID LDS window width in cells (0 = the largest that fits,
-                               centred on the grid; by library choice with sides after the shower axis) */
+                               fits beside the blocks that a CU runs together, else a window of it;
+                               SPHERES: the whole sphere array, an error if it does not fit),
+                               0 = global atomics only, -1 = library choice */
+  int32_t hist_window;      /* tuning: GRID LDS window width in cells (0 = the largest that fits
+                               beside those blocks, centred on the grid; by library choice with
+                               sides after the shower axis) */
   int32_t hist_window_h;    /* tuning: GRID LDS window height in cells (0 = hist_window: a square); a
-                               window larger than the LDS allows is shrunk to fit, and one that leaves
-                               LDS unused is grown about its centre */
+                               window larger than the LDS allows at two waves per SIMD is shrunk to
+                               fit, and one that leaves LDS unused is grown about its centre */
   int32_t hist_window_dx;   /* tuning: GRID LDS window centre minus grid centre, cells along x (0 =
                                centred; clamped so that the window stays inside the grid) */
   int32_t hist_window_dy;   /* tuning: the same along y */

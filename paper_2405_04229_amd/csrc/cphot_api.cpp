@@ -512,6 +512,10 @@ int choose_shape(const cphot_detector* det, cphot::KParams& p, int mode, LaunchS
       const size_t worth = (size_t)(p.n / std::max<int64_t>(blocks, 1)) * 4;
       if (w > 0 && h > 0) grow_window(w, h, p.nx, p.ny, std::min(room(per_cu), worth));
     } else {
+      // Fewer blocks on a CU only where they leave a window of less than 4096 cells: a grid
+      // that fewer blocks would hold whole loses more by them than by its atomics (90 x 90
+      // cells in blocks of 128, six on a CU and three, 2e6 segments straight 848 and
+      // 1304 us, table 1700 and 2285; 120 x 120 in blocks of 256, four and two, 723 and 1017).
       while (per_cu > 1 && room(per_cu) < std::min<size_t>(whole, 4096)) --per_cu;
       const size_t area = room(per_cu);
       if (whole > area) {
