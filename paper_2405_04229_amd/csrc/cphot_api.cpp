@@ -566,6 +566,15 @@ int choose_shape(const cphot_detector* det, cphot::KParams& p, int mode, LaunchS
       p.hist_words = (int32_t)(nsph * (1 + (size_t)p.hist_tw));
     }
   }
+  if (own && !p.lds_hist) {
+    // Counts that do not fit in LDS: nothing is left for the waves of a large block to share,
+    // which then holds its CU until its last wave ends. Blocks of 256 (62,500 spheres, 1e6
+    // segments: network 1,786 -> 1,495 us, layered 1,426 -> 1,357, straight 1,406 -> 1,383).
+    cphot_detector d = *det;
+    d.block_size = 256;
+    d.lds_hist = 0;
+    return choose_shape(&d, p, mode, s);
+  }
   const int64_t tiles = (p.n + 63) / 64;
   const int64_t fill = cus * per_cu * waves;  // waves on the chip
   if (mode != cphot::MODE_COUNTS) p.sub_shift = work_shift(det, tiles, fill);
