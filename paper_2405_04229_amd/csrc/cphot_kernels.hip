@@ -1029,13 +1029,13 @@ __device__ void flush_window(const KParams& p, uint32_t* s_hist, const Window& w
     else atomicAdd(reinterpret_cast<uint32_t*>(p.bins) + gb, (uint32_t)w);
   };
   if constexpr (DETECTOR == CPHOT_DETECTOR_GRID) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t base = (int64_t)sh * p.nx * p.ny;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, row = p.nx;
+    const int64_t base = (int64_t)sh * row * p.ny;
     for (int ly = wave; ly < win.h; ly += BS / 64) {
       for (int lx = lane; lx < win.w; lx += 64) {
         const uint32_t v = s_hist[ly * win.w + lx];
         if (v) {
-          add(base + (int64_t)(win.y0 + ly) * p.nx + (win.x0 + lx), v);
+          add(base + (int64_t)(win.y0 + ly) * row + (win.x0 + lx), v);
           s_hist[ly * win.w + lx] = 0u;
         }
       }
