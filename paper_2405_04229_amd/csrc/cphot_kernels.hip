@@ -1117,7 +1117,7 @@ __global__ __launch_bounds__(BS, (kMinWaves<BS, TRANSPORT>)) void k_propagate(KP
   // directly. Without it every hit is a device atomic, and hits on one sphere
   // serialise on its cache line.
   extern __shared__ uint32_t s_hist[];
-  __shared__ unsigned long long s_since;  // records counted in the window since the last flush
+  __shared__ unsigned long long s_since;  // records counted in the window since it was clear, at most
   __shared__ uint32_t s_next;             // next unit of the block's run, from its first
   // segments of the run's shower (kept where batches run; in the curved kernels the few
   // registers it takes cost 1 %)
@@ -1344,15 +1344,16 @@ __global__ __launch_bounds__(BS, (kMinWaves<BS, TRANSPORT>)) void k_propagate(KP
         const uint32_t end_ch = wave_scan_add(n_ch), end_fl = wave_scan_add(n_fl);
         const uint32_t total_ch = (uint32_t)__builtin_amdgcn_readlane((int)end_ch, 63);
         const uint32_t total_fl = (uint32_t)__builtin_amdgcn_readlane((int)end_fl, 63);
-        // per wave at most 64 << 22 records in a tile; window counts stay below 2^32
-        // because a tile that could take them beyond goes to the global bins directly
+        // Window counts stay below 2^32: a block whose units of one shower could take them beyond
+        // 2^31 leaves its window for the global bins, until the next shower. A CU needs some ten
+        // seconds for that many records.
         bool use_win = n_hist != 0 && S.sh == win_sh;
         if (use_win) {
-          unsigned long long was = 0;
-          if (lane == 0) was = atomicAdd(&s_since, (unsigned long long)total_ch + total_fl);
-          use_win = !__builtin_amdgcn_readfirstlane((int)(was + total_ch + total_fl > (1ull << 31)));
+          unsigned long long sum = ((total_ch + total_fl) >> sub) + 192u;  // no unit of the tile has more
+          if (lane == 0) sum += atomicAdd(&s_since, sum);
+          use_win = !__builtin_amdgcn_readfirstlane((int)(sum > (1ull << 31)));
         }
-        // ---- 3. rounds of 64 records, Cherenkov rounds first (at most 2^23, 2^8 shares)
+        // ---- 3. rounds of 64 records, Cherenkov rounds first (at most 2^22, 2^5 shares)
         const uint32_t rounds_ch = (total_ch + 63) >> 6, rounds = rounds_ch + ((total_fl + 63) >> 6);
         const uint32_t r_first = rounds * share >> sub, r_end = rounds * (share + 1) >> sub;
         uint32_t done = 0, culled = 0, fallback = 0, not_emitted = 0;  // the same in every lane
