@@ -88,13 +88,19 @@ def sources_sha():
     return h.hexdigest()[:16]
 
 
+def launch_block(tune):
+    """Threads per block of the exact tracers' kernel at a tuned shape: the library's own shape
+    (grid_blocks -1) is one block of 1024 per CU."""
+    return 1024 if int(tune["grid_blocks"]) < 0 else int(tune["block_size"])
+
+
 def measured_if_current(key, tune):
     m = MEASURED.get(key)
     if not m or m["sha"] != sources_sha():
         return None
     # the kernel variant (block size) and the histogram mode fix the instructions issued per launch;
     # the grid size and the window change them by under 1 % (the autotuner trials of one variant)
-    if (int(tune["block_size"]), int(tune["lds_hist"])) != (m["shape"][0], m["shape"][2]):
+    if (launch_block(tune), int(tune["lds_hist"])) != (m["shape"][0], m["shape"][2]):
         return None
     return m
 
@@ -253,7 +259,7 @@ def bench_inclined(torch, cphot, W, args, stream):
     log(f"inclined exact: {ms:.3f} ms/step, kernel {kern:.3f} ms, {records:.4g} records")
     dh = W.ATMO_LAYERED["h_top"] / W.ATMO_LAYERED["n_layers"]
     cross, _ = crossing_profile(torch, cphot, sh.seg, geom, det, run["h_obs"], dh, W.ATMO_LAYERED["n_layers"], True)
-    roof = roofline_entry(f"k_propagate<{tune['block_size']},CURVED,GRID,PROPAGATE>", kern, float(sh.n),
+    roof = roofline_entry(f"k_propagate<{launch_block(tune)},CURVED,GRID,PROPAGATE>", kern, float(sh.n),
                           SEGMENT_BYTES_DEDX, records, cross, True, tune, "inclined_curved")
     head = {"value": photons / (ms * 1e-3), "ms_per_step": ms, "kernel_ms": kern, "records": records,
             "photons": photons, "segments": sh.n, "fluorescence_records": float(c[10]),
@@ -533,7 +539,7 @@ def bench_telescope(torch, cphot, W, args, stream):
            "records_per_step": records, "photons_per_step": photons, "segments_per_s": sh.n / (ms * 1e-3),
            "workload": f"1e6 segments, zenith 20 deg, Xmax 400, beta variant {args.beta}, 100 layers x 64 "
                        "wavelength bins, bunch 5, 10x10 spheres r=6 m pitch 150 m, 512 x 1 ns time bins",
-           "roofline": roofline_entry(f"k_propagate<{tune['block_size']},LAYERED,SPHERES,PROPAGATE>", kern,
+           "roofline": roofline_entry(f"k_propagate<{launch_block(tune)},LAYERED,SPHERES,PROPAGATE>", kern,
                                       float(sh.n), SEGMENT_BYTES, records, cross, False, tune, "telescope_layered")}
     shape = {k: tune[k] for k in ("block_size", "grid_blocks", "lds_hist")}
     if not args.no_cuts:
@@ -873,7 +879,10 @@ def block_balance(torch, cphot, S, det, n, tune):
     c = counts.cpu().numpy().astype(np.int64)
     tiles = np.add.reduceat(c, np.arange(0, n, 64))  # a tile is a wave's 64 segments
     nt = len(tiles)
-    grid = min(int(tune["grid_blocks"]), nt)
+    grid = int(tune["grid_blocks"])
+    if grid < 0:  # the library's own shape: a block per CU
+        grid = torch.cuda.get_device_properties(0).multi_processor_count
+    grid = min(grid, nt)
     first = (np.arange(grid, dtype=np.int64) * nt) // grid
     per_block = np.add.reduceat(tiles, first)
     mean = float(per_block.mean())

@@ -260,7 +260,9 @@ typedef struct {
                                stochastically; CPHOT_COUNTS_POISSON: drawn from Poisson(mu) */
   double time_bin_ns;       /* width of a time bin, ns */
   int32_t block_size;       /* tuning: threads per block (0 = library choice) */
-  int32_t grid_blocks;      /* tuning: blocks of the persistent grid (0 = library choice) */
+  int32_t grid_blocks;      /* tuning: blocks of the persistent grid (0 = library choice; -1 = the
+                               library's own shape, as with block_size and grid_blocks 0, whatever
+                               block_size is) */
   int32_t lds_hist;         /* tuning: 1 = privatise the counts in LDS (GRID: the whole grid if it
                                fits beside the blocks that a CU runs together, else a window of it;
                                SPHERES: the whole sphere array, an error if it does not fit),
@@ -400,7 +402,7 @@ void cphot_step_destroy(cphot_step* step);
 /* Result of cphot_autotune: the launch shape to put into cphot_detector. */
 typedef struct {
   int32_t block_size;
-  int32_t grid_blocks;   /* 0 = the library's choice */
+  int32_t grid_blocks;   /* 0 = the library's choice, -1 = the library's own shape */
   int32_t lds_hist;
   int32_t bunch;
   int32_t hist_window;   /* LDS window width in cells (0 with lds_hist 0) */
@@ -410,13 +412,13 @@ typedef struct {
   int32_t hist_window_dx, hist_window_dy;  /* window centre minus grid centre, cells */
 } cphot_tuning;
 
-/* Times cphot_propagate over candidate launch shapes (block size 128 / 256 /
- * 512; one block per tile or a persistent grid of 2, 3, 4 or 8 blocks per CU; LDS grid
- * histogram off, or on with the whole grid when it fits, else with windows:
- * the largest centred square, and rectangles fitted to the photon footprint of
- * a pilot launch (global atomics only; counts summed over showers): for a few
- * areas up to the LDS budget and aspect ratios from 1:4 to 4:1, the rectangle
- * that holds the most photons) and over the bunch sizes in
+/* Times cphot_propagate over candidate launch shapes (the library's own; block
+ * size 128 / 256 / 512 with the library's grid or 2, 3, 4 or 8 blocks per CU and the
+ * LDS grid histogram off, or on with the library's window, a centred square, and
+ * rectangles fitted to the photon footprint of a pilot launch (global atomics only;
+ * counts summed over showers): for a few areas up to the LDS budget and aspect
+ * ratios from 1:4 to 4:1, the rectangle that holds the most photons) and over the
+ * bunch sizes in
  * `bunch_candidates` (n_bunch values >= 1; NULL = the detector's own), `reps`
  * timed launches each after one warm-up, and returns the shape and bunch with
  * the most photons per second. Larger bunches trade statistical resolution for

@@ -476,7 +476,7 @@ int choose_shape(const cphot_detector* det, cphot::KParams& p, int mode, LaunchS
   if (det->hist_window < 0 || det->hist_window_h < 0)
     return fail(CPHOT_ERR_INVALID_ARG, "hist_window and hist_window_h must be >= 0");
   const bool propagate = mode == cphot::MODE_PROPAGATE, on_grid = p.detector == CPHOT_DETECTOR_GRID;
-  const bool own = propagate && det->block_size == 0 && det->grid_blocks <= 0 &&
+  const bool own = propagate && (det->grid_blocks < 0 || (det->block_size == 0 && det->grid_blocks == 0)) &&
                    (on_grid ? det->lds_hist != 0 && det->hist_window == 0 : det->lds_hist < 0);
   const int bs = own ? cphot::kBigBlock : det->block_size ? det->block_size : 256;
   int dev = 0;
@@ -1302,15 +1302,70 @@ int cphot_autotune(const cphot_segments* seg, const cphot_detector* det, cphot_b
   std::vector<double> foot;
   if (det->detector == CPHOT_DETECTOR_GRID && det->lds_hist != 0 && (int64_t)det->nx * det->ny > 4096)
     rc = grid_footprint(seg, det, out, st, foot);
+  // Times one launch shape; `tried` (if given) holds those already timed at its block size.
+  auto trial = [&](const cphot_detector& d, std::vector<std::array<int, 6>>* tried) -> int {
+    cphot::KParams p;
+    int err = fill_params(seg, &d, p, true, out);
+    if (err || p.n == 0) return err;
+    LaunchShape sh;
+    if (choose_shape(&d, p, cphot::MODE_PROPAGATE, sh) != CPHOT_OK) return CPHOT_OK;  // e.g. no window fits
+    if (tried) {  // skip shapes that came out the same
+      const std::array<int, 6> key = {sh.grid, p.lds_hist, p.hist_w, p.hist_h, p.hist_x0, p.hist_y0};
+      if (std::find(tried->begin(), tried->end(), key) != tried->end()) return CPHOT_OK;
+      tried->push_back(key);
+    }
+    hipError_t e = clear_outputs(out, st);
+    if (e == hipSuccess) e = cphot::launch_propagate(p, cphot::MODE_PROPAGATE, sh.block, sh.grid, sh.lds, st);
+    if (e == hipSuccess) e = clear_outputs(out, st);
+    if (e == hipSuccess) e = hipEventRecord(e0, st);
+    for (int r = 0; r < reps && e == hipSuccess; ++r)
+      e = cphot::launch_propagate(p, cphot::MODE_PROPAGATE, sh.block, sh.grid, sh.lds, st);
+    if (e == hipSuccess) e = hipEventRecord(e1, st);
+    if (e == hipSuccess) e = hipEventSynchronize(e1);
+    float ms = 0.f;
+    if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+    unsigned long long gen = 0;
+    if (e == hipSuccess)
+      e = hipMemcpy(&gen, out->counters + CPHOT_C_RECORDS_GENERATED, sizeof(gen), hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return hip_fail(e, "autotune trial");
+    const double t = ms / reps;
+    const double pps = (double)gen / reps * d.bunch / (t * 1e-3);
+    if (pps > top.photons_per_s) {
+      top.block_size = d.block_size;
+      // a persistent grid by library choice is reported with its block count
+      top.grid_blocks = (d.grid_blocks == 0 && p.lds_hist && p.detector == CPHOT_DETECTOR_GRID) ? sh.grid
+                                                                                               : d.grid_blocks;
+      top.lds_hist = d.lds_hist;
+      const bool window = d.lds_hist == 1;
+      top.hist_window = window ? p.hist_w : 0;
+      top.hist_window_h = window ? p.hist_h : 0;
+      top.hist_window_dx = window ? p.hist_x0 - (p.nx - p.hist_w) / 2 : 0;
+      top.hist_window_dy = window ? p.hist_y0 - (p.ny - p.hist_h) / 2 : 0;
+      top.bunch = d.bunch;
+      top.ms = t;
+      top.photons_per_s = pps;
+    }
+    return CPHOT_OK;
+  };
   for (int32_t b : bunches) {
+    if (rc != CPHOT_OK) break;
+    {  // the library's own shape, which no block size of the others gives
+      cphot_detector d = *det;
+      d.bunch = b;
+      d.block_size = 512;
+      d.grid_blocks = -1;
+      d.lds_hist = -1;
+      d.hist_window = d.hist_window_h = d.hist_window_dx = d.hist_window_dy = 0;
+      rc = trial(d, nullptr);
+    }
     for (int bs : {128, 256, 512}) {
       std::vector<std::array<int, 6>> tried;  // launches already timed at this block size
-      // grids: one block per tile, or a persistent grid of 2, 3, 4 or 8 blocks per CU (more
-      // blocks than fit at once: the dispatcher starts later ones as earlier ones finish)
+      // the library's grid for the block size, or 2, 3, 4 or 8 blocks per CU (more than
+      // run at a time: later ones start as earlier ones finish)
       for (int gpol = 0; gpol < 5 && rc == CPHOT_OK; ++gpol) {
-        // LDS histogram: off; the largest centred square that fits; a centred 64 x 64;
-        // rectangles fitted to the footprint with up to 2304, 4096 and 9216 cells
-        // and with all the room the block's LDS budget leaves
+        // LDS histogram: off; the library's window; a centred 64 x 64; rectangles fitted to
+        // the footprint with up to 2304, 4096 and 9216 cells and with all the room that two
+        // waves per SIMD leave
         std::vector<Window> wins = {{-1, 0, 0, 0}, {0, 0, 0, 0}, {64, 64, 0, 0}};
         if (!foot.empty()) {
           cphot_detector d = *det;
@@ -1335,54 +1390,7 @@ int cphot_autotune(const cphot_segments* seg, const cphot_detector* det, cphot_b
           d.hist_window_h = win.w < 0 ? 0 : win.h;
           d.hist_window_dx = win.w < 0 ? 0 : win.dx;
           d.hist_window_dy = win.w < 0 ? 0 : win.dy;
-          cphot::KParams p;
-          if ((rc = fill_params(seg, &d, p, true, out))) break;
-          if (p.n == 0) break;
-          LaunchShape sh;
-          if (choose_shape(&d, p, cphot::MODE_PROPAGATE, sh) != CPHOT_OK) {
-            rc = CPHOT_OK;  // shape not applicable (e.g. no window fits)
-            continue;
-          }
-          {  // skip shapes that came out the same as one already timed
-            const std::array<int, 6> key = {sh.grid, p.lds_hist, p.hist_w, p.hist_h, p.hist_x0, p.hist_y0};
-            bool seen = false;
-            for (const auto& k : tried) seen = seen || k == key;
-            if (seen) continue;
-            tried.push_back(key);
-          }
-          hipError_t e = clear_outputs(out, st);
-          if (e == hipSuccess) e = cphot::launch_propagate(p, cphot::MODE_PROPAGATE, sh.block, sh.grid, sh.lds, st);
-          if (e == hipSuccess) e = clear_outputs(out, st);
-          if (e == hipSuccess) e = hipEventRecord(e0, st);
-          for (int r = 0; r < reps && e == hipSuccess; ++r)
-            e = cphot::launch_propagate(p, cphot::MODE_PROPAGATE, sh.block, sh.grid, sh.lds, st);
-          if (e == hipSuccess) e = hipEventRecord(e1, st);
-          if (e == hipSuccess) e = hipEventSynchronize(e1);
-          float ms = 0.f;
-          if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
-          unsigned long long gen = 0;
-          if (e == hipSuccess)
-            e = hipMemcpy(&gen, out->counters + CPHOT_C_RECORDS_GENERATED, sizeof(gen), hipMemcpyDeviceToHost);
-          if (e != hipSuccess) {
-            rc = hip_fail(e, "autotune trial");
-            break;
-          }
-          const double t = ms / reps;
-          const double pps = (double)gen / reps * b / (t * 1e-3);
-          if (pps > top.photons_per_s) {
-            top.block_size = bs;
-            // a persistent grid by library choice is reported with its block count
-            top.grid_blocks = (d.grid_blocks == 0 && p.lds_hist && p.detector == CPHOT_DETECTOR_GRID) ? sh.grid
-                                                                                                     : d.grid_blocks;
-            top.lds_hist = d.lds_hist;
-            top.hist_window = d.lds_hist ? p.hist_w : 0;
-            top.hist_window_h = d.lds_hist ? p.hist_h : 0;
-            top.hist_window_dx = d.lds_hist ? p.hist_x0 - (p.nx - p.hist_w) / 2 : 0;
-            top.hist_window_dy = d.lds_hist ? p.hist_y0 - (p.ny - p.hist_h) / 2 : 0;
-            top.bunch = b;
-            top.ms = t;
-            top.photons_per_s = pps;
-          }
+          rc = trial(d, &tried);
         }
       }
     }
@@ -1412,7 +1420,8 @@ TuneCache& tune_cache() {
 
 // Everything the best launch shape can depend on, except the launch shape itself:
 // device, atmosphere layout, detector settings, segment and shower counts, the
-// candidate bunches and the number of timed launches.
+// candidate bunches and the number of timed launches. The figure after the ABI version counts
+// the sets of shapes: entries found among fewer are not used.
 std::string tune_signature(const cphot_segments* seg, const cphot_detector* det, const int32_t* bunches,
                            int32_t n_bunch, int32_t reps) {
   int dev = 0;
@@ -1423,7 +1432,7 @@ std::string tune_signature(const cphot_segments* seg, const cphot_detector* det,
   const cphot_atmosphere_desc& a = det->atm->d;
   char buf[1024];
   std::snprintf(buf, sizeof(buf),
-                "abi%d;%s;cu%d;atm%d,%d,%d,%.9g,%.9g,%.9g;t%d;d%d;s%d;e%d;c%d;cuts%d;b%d;h%.9g;g%d,%d,%.9g;"
+                "abi%d.2;%s;cu%d;atm%d,%d,%d,%.9g,%.9g,%.9g;t%d;d%d;s%d;e%d;c%d;cuts%d;b%d;h%.9g;g%d,%d,%.9g;"
                 "sp%d,%d,%.9g,%.9g;nt%d,%.9g;eff%d;red%d;sur%d;tab%d;n%lld;ns%lld;reps%d;bunches",
                 CPHOT_ABI_VERSION, name.c_str(), cu_count(dev), a.profile, a.n_layers, a.n_lambda_bins, a.h_top,
                 a.lambda_min_nm, a.lambda_max_nm, det->transport, det->detector, det->spectrum, det->emission,
