@@ -566,10 +566,17 @@ int choose_shape(const cphot_detector* det, cphot::KParams& p, int mode, LaunchS
       p.hist_words = (int32_t)(nsph * (1 + (size_t)p.hist_tw));
     }
   }
-  if (own && !p.lds_hist) {
-    // Counts that do not fit in LDS: nothing is left for the waves of a large block to share,
-    // which then holds its CU until its last wave ends. Blocks of 256 (62,500 spheres, 1e6
-    // segments: network 1,786 -> 1,495 us, layered 1,426 -> 1,357, straight 1,406 -> 1,383).
+  // Sphere arrays of many short showers: a block flushes its array and waits for its last wave at
+  // each shower, some 4 us, and an array that few photons hit gains nothing by LDS. The line lies
+  // at 1000 expected hits a shower (1000 showers of 100 segments on 100 spheres of 6 m, 4 hits
+  // each: 73 us, with device atomics 39; of 300 on 400 spheres of 12 m, 2,000: 241 and 401).
+  const bool few_hits = !on_grid && p.n_showers > 1 &&
+                        (double)p.n / p.n_showers * rounds_per_tile(det) * M_PI * det->radius * det->radius <
+                            1000.0 * det->pitch * det->pitch;
+  if (own && (!p.lds_hist || few_hits)) {
+    // Without LDS counts nothing is left for the waves of a large block to share, which then
+    // holds its CU until its last wave ends. Blocks of 256 (62,500 spheres, 1e6 segments:
+    // network 1,786 -> 1,495 us, layered 1,426 -> 1,357, straight 1,406 -> 1,383).
     cphot_detector d = *det;
     d.block_size = 256;
     d.lds_hist = 0;
