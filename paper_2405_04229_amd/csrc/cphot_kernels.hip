@@ -1326,6 +1326,17 @@ __global__ __launch_bounds__(BS, (kMinWaves<BS, TRANSPORT>)) void k_propagate(KP
         todo &= ~__ballot(mine);
         n_ch = mine ? all_ch : 0u;
         n_fl = mine ? all_fl : 0u;
+        const uint32_t end_ch = wave_scan_add(n_ch), end_fl = wave_scan_add(n_fl);
+        const uint32_t total_ch = (uint32_t)__builtin_amdgcn_readlane((int)end_ch, 63);
+        const uint32_t total_fl = (uint32_t)__builtin_amdgcn_readlane((int)end_fl, 63);
+        // ---- 3. rounds of 64 records, Cherenkov rounds first (at most 2^22, 2^5 shares). The
+        // shares go round with the showers, so that showers of a round or two, many in a tile,
+        // are spread over its units (100 showers of a segment each 112 -> 36 us, through the
+        // network 253 -> 71).
+        const uint32_t rounds_ch = (total_ch + 63) >> 6, rounds = rounds_ch + ((total_fl + 63) >> 6);
+        const uint32_t part = (share + ((uint32_t)S.sh << (sub - p.sub_shift))) & ((1u << sub) - 1u);
+        const uint32_t r_first = rounds * part >> sub, r_end = rounds * (part + 1) >> sub;
+        if (r_first == r_end) continue;
         {
           const double* g = p.geom + 5 * (int64_t)S.sh;
           S.core_x = uniform((float)g[0]);
@@ -1341,9 +1352,6 @@ __global__ __launch_bounds__(BS, (kMinWaves<BS, TRANSPORT>)) void k_propagate(KP
             S.axz = uniform((float)g[4]);
           }
         }
-        const uint32_t end_ch = wave_scan_add(n_ch), end_fl = wave_scan_add(n_fl);
-        const uint32_t total_ch = (uint32_t)__builtin_amdgcn_readlane((int)end_ch, 63);
-        const uint32_t total_fl = (uint32_t)__builtin_amdgcn_readlane((int)end_fl, 63);
         // Window counts stay below 2^32: a block whose units of one shower could take them beyond
         // 2^31 leaves its window for the global bins, until the next shower. A CU needs some ten
         // seconds for that many records.
@@ -1353,9 +1361,6 @@ __global__ __launch_bounds__(BS, (kMinWaves<BS, TRANSPORT>)) void k_propagate(KP
           if (lane == 0) sum += atomicAdd(&s_since, sum);
           use_win = !__builtin_amdgcn_readfirstlane((int)(sum > (1ull << 31)));
         }
-        // ---- 3. rounds of 64 records, Cherenkov rounds first (at most 2^22, 2^5 shares)
-        const uint32_t rounds_ch = (total_ch + 63) >> 6, rounds = rounds_ch + ((total_fl + 63) >> 6);
-        const uint32_t r_first = rounds * share >> sub, r_end = rounds * (share + 1) >> sub;
         uint32_t done = 0, culled = 0, fallback = 0, not_emitted = 0;  // the same in every lane
         uint32_t packed = 0, in_packed = 0;  // this lane's counts of states 0..3, 8 bits each; additions since the last unpacking
         auto unpack = [&]() {
