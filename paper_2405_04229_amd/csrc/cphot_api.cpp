@@ -583,7 +583,8 @@ int choose_shape(const cphot_detector* det, cphot::KParams& p, int mode, LaunchS
     return choose_shape(&d, p, mode, s);
   }
   const int64_t tiles = (p.n + 63) / 64;
-  const int64_t fill = cus * per_cu * waves;  // waves on the chip
+  // waves on the chip, or those of the caller's grid where it is smaller
+  const int64_t fill = (det->grid_blocks > 0 ? std::min<int64_t>(det->grid_blocks, cus * per_cu) : cus * per_cu) * waves;
   if (mode != cphot::MODE_COUNTS) p.sub_shift = work_shift(det, tiles, fill);
   // blocks that find a unit for each wave; of the large blocks, where a launch has fewer
   // units than the chip has waves, for each fourth: more CUs with fewer waves each (1e4
