@@ -1329,12 +1329,15 @@ __global__ __launch_bounds__(BS, (kMinWaves<BS, TRANSPORT>)) void k_propagate(KP
         const uint32_t end_ch = wave_scan_add(n_ch), end_fl = wave_scan_add(n_fl);
         const uint32_t total_ch = (uint32_t)__builtin_amdgcn_readlane((int)end_ch, 63);
         const uint32_t total_fl = (uint32_t)__builtin_amdgcn_readlane((int)end_fl, 63);
-        // ---- 3. rounds of 64 records, Cherenkov rounds first (at most 2^22, 2^5 shares). The
-        // shares go round with the showers, so that showers of a round or two, many in a tile,
-        // are spread over its units (100 showers of a segment each 112 -> 36 us, through the
-        // network 253 -> 71).
+        // ---- 3. rounds of 64 records, Cherenkov rounds first (at most 2^22, 2^5 shares). In a
+        // tile of several showers the shares go round with the shower, so that showers of a
+        // round or two are spread over its units (100 showers of a segment each 112 -> 36 us,
+        // through the network 253 -> 71). A tile of one shower is not turned: the same share of
+        // every tile then has the longer end (100 curved showers of 64 segments 82 -> 66 us).
         const uint32_t rounds_ch = (total_ch + 63) >> 6, rounds = rounds_ch + ((total_fl + 63) >> 6);
-        const uint32_t part = (share + ((uint32_t)S.sh << (sub - p.sub_shift))) & ((1u << sub) - 1u);
+        uint32_t part = share;
+        if (p.n_showers > 1 && __ballot((all_ch | all_fl) != 0u && !mine))
+          part = (share + ((uint32_t)S.sh << (sub - p.sub_shift))) & ((1u << sub) - 1u);
         const uint32_t r_first = rounds * part >> sub, r_end = rounds * (part + 1) >> sub;
         if (r_first == r_end) continue;
         {
