@@ -70,12 +70,12 @@ METRIC = "photons propagated/s, exact vs MLP surrogate, at <=1% per-bin density 
 KERNEL_SOURCES = ("cphot_kernels.hip", "cphot_device.h", "cphot_internal.h", "cphot_mlp.h")
 MEASURED = {
     # profiles/k_propagate_curved_inclined_1e7.md: mean of the six launches of the timed step
-    "inclined_curved": {"sha": "053626bff79a0339", "shape": [512, 2048, 1, 143, 73, 0, 0],
-                        "valu_insts": 7.0622479e9, "hbm_bytes": (176792.59 * 2.0 + 433190.5 * 1.0) * 1024,
+    "inclined_curved": {"sha": "1c405a7190b04865", "shape": [1024, -1, -1, 0, 0, 0, 0],
+                        "valu_insts": 7.1311199e9, "hbm_bytes": (177085.97 * 2.0 + 385393.44 * 1.0) * 1024,
                         "profile": "profiles/k_propagate_curved_inclined_1e7.md"},
     # profiles/k_propagate_telescope_1e6.md: mean of the six launches of the timed step
-    "telescope_layered": {"sha": "053626bff79a0339", "shape": [256, 1024, 1, 0, 0, 0, 0],
-                          "valu_insts": 6.6452517e7, "hbm_bytes": (16247.473 * 2.0 + 288.0 * 1.0) * 1024,
+    "telescope_layered": {"sha": "1c405a7190b04865", "shape": [256, 1024, 1, 0, 0, 0, 0],
+                          "valu_insts": 6.5900403e7, "hbm_bytes": (16250.125 * 2.0 + 288.0 * 1.0) * 1024,
                           "profile": "profiles/k_propagate_telescope_1e6.md"},
 }
 
